@@ -124,7 +124,6 @@ bwd_main_kernel(const BArgs a) {
   const rsrc_t Ox = make_rsrc(a.dX ? a.dX + bh * T * D : nullptr, a.dX ? (uint32_t)(T * D * 4) : 0u);
   const rsrc_t Od = make_rsrc(a.dG ? a.dG + bh * T * M : nullptr, a.dG ? (uint32_t)(T * M * 4) : 0u);
   const rsrc_t Oe = make_rsrc(a.deta ? a.deta + bh * T : nullptr, a.deta ? (uint32_t)(T * 4) : 0u);
-  const rsrc_t none = make_rsrc(nullptr, 0u);  // every access out of range
   const int64_t nch = (t_end - t_begin + C - 1) / C;
 
   // Register staging, DEPTH chunks ahead (chunks are visited last to first).
@@ -230,8 +229,6 @@ bwd_main_kernel(const BArgs a) {
   }
 
   auto chunk = [&](TX& xr, TM& gr, TM& dr, EtaReg<ETAV>& er, RstReg<RST>& rr, int64_t n) {
-    // A step before the segment start (the second of a pair) sees zero
-    // tiles, leaves W and R unchanged and stores nothing.
     // Lane and thread indices as the chunk sees them: opaque to the compiler,
     // so that LDS addresses are formed per use instead of being hoisted out
     // of the loop into dozens of live registers.
@@ -256,9 +253,7 @@ bwd_main_kernel(const BArgs a) {
       nM[e] = PRE ? lM.nat_rt(0, 16 * blk(e)) : 0;
     }
     const int64_t t0 = t_begin + n * C;
-    const bool live = n >= 0;
-    const int nvalid = live ? (int)(t_end - t0 < C ? t_end - t0 : C) : 0;
-    const rsrc_t Ogc = live ? Og : none, Oxc = live ? Ox : none, Odc = live ? Od : none, Oec = live ? Oe : none;
+    const int nvalid = (int)(t_end - t0 < C ? t_end - t0 : C);
     __syncthreads();
     er.stage(et, C, a.eta_scalar, nvalid, 1.f, td);
     xr.store(Xs, td);
@@ -268,7 +263,7 @@ bwd_main_kernel(const BArgs a) {
     // Reset masks of this chunk (fr = C, lr = -1 without a reset).
     const uint64_t dm = rr.mask();
     const int fr = first_flag(dm), lr = last_flag(dm);
-    const bool has = RST && lr >= 0 && live;
+    const bool has = RST && lr >= 0;
     if (ETAV) gr.store_scaled(Vh, Vl, td, et);  // read after the next barrier
     fetch(xr, gr, dr, er, rr, n - DEPTH);
     // The chunk's compute, compiled with the reset masks (HAS) for the chunks
@@ -499,18 +494,18 @@ bwd_main_kernel(const BArgs a) {
           f32x4 lo, hi;
           if (a.gtilde) {
             pair_rows(ga[0][hh], ga[1][hh], lo, hi);
-            buf_store4(Ogc, o, lo);
-            buf_store4(Ogc, o8, hi);
+            buf_store4(Og, o, lo);
+            buf_store4(Og, o8, hi);
           }
           if (FULL && a.dX) {
             pair_rows(ga[0][hh] - xa2[0][hh], ga[1][hh] - xa2[1][hh], lo, hi);
-            buf_store4(Oxc, o, lo);
-            buf_store4(Oxc, o8, hi);
+            buf_store4(Ox, o, lo);
+            buf_store4(Ox, o8, hi);
           }
         } else {
           const uint32_t o = (uint32_t)(((t0 + 16 * tb + c) * D + 16 * w + 4 * q) * 4);
-          if (a.gtilde) buf_store4(Ogc, o, ga[0][hh]);
-          if (FULL && a.dX) buf_store4(Oxc, o, ga[0][hh] - xa2[0][hh]);
+          if (a.gtilde) buf_store4(Og, o, ga[0][hh]);
+          if (FULL && a.dX) buf_store4(Ox, o, ga[0][hh] - xa2[0][hh]);
         }
       }
     }
@@ -630,10 +625,10 @@ bwd_main_kernel(const BArgs a) {
               const uint32_t o = pair_off(t0 + 16 * sb, 32 * (w >> 1), M, c, q);
               f32x4 lo, hi;
               pair_rows(-es * ua[0][hh], -es * ua[1][hh], lo, hi);
-              buf_store4(Odc, o, lo);
-              buf_store4(Odc, o + 8 * M * 4, hi);
+              buf_store4(Od, o, lo);
+              buf_store4(Od, o + 8 * M * 4, hi);
             } else {
-              buf_store4(Odc, (uint32_t)(((t0 + s) * M + 16 * w + 4 * q) * 4), -es * ua[0][hh]);
+              buf_store4(Od, (uint32_t)(((t0 + s) * M + 16 * w + 4 * q) * 4), -es * ua[0][hh]);
             }
           }
           if (a.deta) {
@@ -654,8 +649,11 @@ bwd_main_kernel(const BArgs a) {
 
     }
     if constexpr (FULL) {
-      // (5) Suffix update: R_{n-1} = R_n + dY^T X (exact products).
-      if (w < JB) {
+      // (5) Suffix update: R_{n-1} = R_n + dY^T X (exact products).  fp32
+      // skips it where neither a next chunk of the walk nor dW0 (at the
+      // sequence's start) reads it: one chunk per segment, 24.4 -> 23.4 us at
+      // T = 256; with bf16's cheaper steps the test cost 0.3 us at lm-bf16.
+      if (w < JB && (OP::kSplit == 2 || n > 0 || (a.rfin && seg == 0))) {
         // With a reset the previous chunk's document ends at the first reset:
         // the suffix restarts from the tokens before it.
         if (HAS)
@@ -684,7 +682,7 @@ bwd_main_kernel(const BArgs a) {
 #pragma unroll
         for (int i = 0; i < (PAIR ? 2 : IB); ++i)
           s += (dpart[i][0][tt] + dpart[i][1][tt]) + (dpart[i][2][tt] + dpart[i][3][tt]);
-        buf_store1(Oec, td < C ? (uint32_t)((t0 + td) * 4) : kOOB, s);
+        buf_store1(Oe, td < C ? (uint32_t)((t0 + td) * 4) : kOOB, s);
       }
     }
       };
@@ -695,6 +693,7 @@ bwd_main_kernel(const BArgs a) {
   if constexpr (DEPTH == 2) {
     for (int64_t n = nch - 1; n >= 0; n -= 2) {
       chunk(xa, ga, da, ea, ra, n);
+      if (n == 0) break;
       chunk(xb, gb, db, eb, rb, n - 1);
     }
   } else {

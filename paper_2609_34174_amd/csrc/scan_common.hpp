@@ -369,9 +369,12 @@ agg_kernel(const KArgs a, int64_t nagg) {
   // T=2048, d=m=64 (forward pass 16.4 -> 15.4 us, backward 18.5 -> 16.5 us
   // against four; one, three, six and eight were slower, and so were two
   // groups of waves per workgroup): more loads in flight per CU only add
-  // concurrent streams.  Every group runs all DEPTH chunk steps (a step past
-  // the segment end sees zero tiles and adds nothing), which keeps the memory
-  // operations branch-free.
+  // concurrent streams.  The register sets are used in turn.  A segment of an
+  // odd number of chunks ends with a step of its own (ODD) where a chunk
+  // costs most, with fp32 tiles and with per-token eta (backward pass of 36
+  // sequences of T = 1999: 14.0 -> 12.2 us); elsewhere it runs the second
+  // set's step on zero tiles, as the extra copy of the step cost the even
+  // segments 0.4 us (1 us with resets).
   constexpr int DEPTH = 2;
   Tile4<OP, C, D, NT> xr[DEPTH];
   Tile4<OP, C, M, NT> gr[DEPTH], dr[DEPTH];
@@ -452,10 +455,14 @@ agg_kernel(const KArgs a, int64_t nagg) {
       }
     }
   };
-  for (int64_t t0 = t_begin; t0 < t_end; t0 += DEPTH * C) {
-#pragma unroll
-    for (int k = 0; k < DEPTH; ++k) chunk(k, t0 + k * C);
+  static_assert(DEPTH == 2, "the walk below takes chunks in pairs");
+  constexpr bool ODD = !RST && (ETAV || OP::kSplit == 1);
+  int64_t t0 = t_begin;
+  for (; t0 + (ODD ? C : 0) < t_end; t0 += 2 * C) {
+    chunk(0, t0);
+    chunk(1, t0 + C);
   }
+  if (ODD && t0 < t_end) chunk(0, t0);
   if (w < IB) {
     // accA[jb] holds A^T[j = 16jb + 4q + r][i = 16w + c].
     const int64_t base = (bh * a.nseg + seg) * M * D;
