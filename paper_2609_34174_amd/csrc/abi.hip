@@ -20,6 +20,7 @@ namespace gradlev {
 namespace {
 
 constexpr int kNumCU = 256;           // MI355X compute units
+constexpr int kXCDs = 8;              // ... on 8 XCDs
 constexpr int64_t kMaxElems = int64_t(1) << 40;
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -42,21 +43,37 @@ struct Plan {
   size_t off_aggA, off_aggB, off_rfin;
 };
 
-int64_t pick_nseg(int64_t BH, int64_t T, int C, int wgs_per_cu, int64_t hint) {
+// Chunks per segment.  Without a hint, the segmentation of least cost by the
+// pass's SegCost: short segments run in parallel but each sums its neighbours'
+// aggregates first, and the work is done when the busiest CU is.  All segments
+// of a sequence stay on one XCD (map_block), so that CU holds
+// ceil(ceil(BH / 8) n / 32) workgroups; one segment count too many can double
+// the time (24 sequences of 1024 tokens, 64 x 64 bf16 backward: 49 us with 16
+// segments each, 48 on an XCD of 32 CUs, 29 us with 8).  Against the rule of
+// ceil(256 w / BH) segments for w workgroups a CU this takes a fifth off the
+// geometric mean over 1 to 256 sequences of 128 to 8000 tokens at the worst
+// widths (bf16 128 x 128 forward) and 4 % at the best.
+// Aggregates (two of `md` bytes per segment, one more per sequence) stay within
+// the static scratch where one segment would not do, so that no call outgrows it.
+int64_t pick_seg_chunks(int64_t BH, int64_t T, int C, size_t md, const SegCost& c, int64_t hint) {
   const int64_t nchunks = (T + C - 1) / C;
-  int64_t seg_chunks;
-  if (hint > 0) {
-    seg_chunks = (hint + C - 1) / C;
-  } else {
-    const int64_t target = (int64_t)kNumCU * wgs_per_cu;
-    int64_t nseg = (target + BH - 1) / BH;
-    if (nseg < 1) nseg = 1;
-    if (nseg > nchunks) nseg = nchunks;
-    if (nseg > 16) nseg = 16;  // a main workgroup sums at most 15 predecessor aggregates
-    seg_chunks = (nchunks + nseg - 1) / nseg;
+  if (hint > 0) return (hint + C - 1) / C;
+  int64_t best = nchunks;
+  double least = 0;
+  for (int64_t n = 1; n <= 16 && n <= nchunks; ++n) {  // a main workgroup sums at most 15 aggregates
+    const int64_t sc = (nchunks + n - 1) / n;
+    if ((nchunks + sc - 1) / sc != n) continue;
+    if (n > 1 && (size_t)((2 * n + 1) * BH) * md > GRADLEV_STATIC_SCRATCH_BYTES) break;
+    const int64_t cus = kNumCU / kXCDs, k = ((BH + kXCDs - 1) / kXCDs * n + cus - 1) / cus;
+    const double g = c.side == 1 ? (double)k : (double)(k / 2) * c.pair + (double)(k % 2);
+    const double len = (double)(sc * C) / 64;
+    const double t = (n == 1 ? c.one : c.pass + c.agg * len) + g * (c.start + c.seg * n + c.chunk * len);
+    if (n == 1 || t < least) {
+      least = t;
+      best = sc;
+    }
   }
-  if (seg_chunks < 1) seg_chunks = 1;
-  return seg_chunks;
+  return best;
 }
 
 // Workspace of a plan: forward segment aggregates; backward aggregates A_k,
@@ -102,14 +119,14 @@ int make_plan(const gradlev_shape* s, Plan* out) {
 
   out->fwd = base;
   out->fwd.chunk = fwd_chunk_for(bf, d, m, (int)s->chunk);
-  int64_t sc = pick_nseg(BH, s->T, out->fwd.chunk, fwd_wgs_per_cu(bf, d, m, out->fwd.chunk), s->segment);
+  int64_t sc = pick_seg_chunks(BH, s->T, out->fwd.chunk, md, fwd_seg_cost(bf, d, m), s->segment);
   out->fwd.seg_len = sc * out->fwd.chunk;
   out->fwd.nseg = (s->T + out->fwd.seg_len - 1) / out->fwd.seg_len;
   if (out->fwd.nseg > 16) return GRADLEV_ERR_UNSUPPORTED;
 
   out->bwd = base;
   out->bwd.chunk = bwd_chunk_for(bf, d, m, (int)s->chunk);
-  sc = pick_nseg(BH, s->T, out->bwd.chunk, bwd_wgs_per_cu(bf, d, m, out->bwd.chunk), s->segment);
+  sc = pick_seg_chunks(BH, s->T, out->bwd.chunk, md, bwd_seg_cost(bf, d, m), s->segment);
   out->bwd.seg_len = sc * out->bwd.chunk;
   out->bwd.nseg = (s->T + out->bwd.seg_len - 1) / out->bwd.seg_len;
   if (out->bwd.nseg > 16) return GRADLEV_ERR_UNSUPPORTED;
@@ -265,7 +282,7 @@ int make_gated_plan(const gradlev_shape* s, GatedPlan* out) {
     ScanProblem& q = k == 0 ? out->fwd : out->bwd;
     q = k == 0 ? base.fwd : base.bwd;
     q.chunk = k == 0 ? gated_fwd_chunk(bf, d, m) : gated_bwd_chunk(bf, d, m);
-    const int64_t sc = pick_nseg(BH, s->T, q.chunk, gated_wgs_per_cu(k == 0, bf, d, m), s->segment);
+    const int64_t sc = pick_seg_chunks(BH, s->T, q.chunk, md, gated_seg_cost(k == 0, bf, d, m), s->segment);
     q.seg_len = sc * q.chunk;
     q.nseg = (s->T + q.seg_len - 1) / q.seg_len;
     if (q.nseg > 16 || !grid_fits(BH, q.nseg)) return GRADLEV_ERR_UNSUPPORTED;
@@ -297,8 +314,8 @@ int make_gated_saved_plan(const gradlev_shape* s, GatedPlan* out, size_t* saved_
   const size_t md = (size_t)s->d_out * s->d_in * sizeof(float);
   const int bf = s->in_dtype == GRADLEV_BF16;
   out->fwd.chunk = out->bwd.chunk;
-  const int64_t sc = pick_nseg(BH, s->T, out->fwd.chunk, gated_wgs_per_cu(1, bf, (int)s->d_in, (int)s->d_out),
-                               s->segment);
+  const int64_t sc = pick_seg_chunks(BH, s->T, out->fwd.chunk, md, gated_seg_cost(1, bf, (int)s->d_in, (int)s->d_out),
+                                     s->segment);
   out->fwd.seg_len = sc * out->fwd.chunk;
   out->fwd.nseg = (s->T + out->fwd.seg_len - 1) / out->fwd.seg_len;
   if (out->fwd.nseg > 16 || !grid_fits(BH, out->fwd.nseg)) return GRADLEV_ERR_UNSUPPORTED;

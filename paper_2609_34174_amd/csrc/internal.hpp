@@ -99,18 +99,30 @@ hipError_t launch_act_bwd(int bf16, const float* Z, float* G, void* Gq, int64_t 
 hipError_t launch_mlp_gate_grads(const float* de1, const float* de2, float s1, float s2, float* dmu,
                                  const float* da1, float* dalpha, int64_t n, hipStream_t s);
 
+// What a scan of n segments costs, in microseconds, as the planner weighs it
+// (pick_seg_chunks): `one` is spent with a single segment, else `pass` plus
+// `agg` per 64 tokens of a segment (the aggregate launch); then the main
+// kernel: `start` and `seg` per segment (its prologue) and `chunk` per 64
+// tokens, times g(k) where k workgroups meet on the busiest CU: each when
+// side == 1, else `pair` for two side by side.
+struct SegCost {
+  float one, pass, agg, start, seg, chunk;
+  int side;
+  float pair;
+};
+
 int gated_fwd_chunk(int bf16, int d, int m);
 int gated_bwd_chunk(int bf16, int d, int m);
-int gated_wgs_per_cu(int fwd, int bf16, int d, int m);
+SegCost gated_seg_cost(int fwd, int bf16, int d, int m);
 hipError_t launch_scan_fwd_gated(const ScanProblem& p, const GatedPtrs& a, hipStream_t s);
 hipError_t launch_scan_bwd_gated(const ScanProblem& p, const GatedPtrs& a, hipStream_t s);
 
 // Tile lengths each kernel family supports for a shape (LDS budget).
 int fwd_chunk_for(int bf16, int d, int m, int requested);
 int bwd_chunk_for(int bf16, int d, int m, int requested);
-// Resident workgroups per CU for the main kernels (LDS bound).
-int fwd_wgs_per_cu(int bf16, int d, int m, int chunk);
-int bwd_wgs_per_cu(int bf16, int d, int m, int chunk);
+// Time of a pass by its segmentation, for the planner.
+SegCost fwd_seg_cost(int bf16, int d, int m);
+SegCost bwd_seg_cost(int bf16, int d, int m);
 
 // Wide maps (parallel form, scan_wide.hip): d and m multiples of 128, at
 // least one above 128; exclusive reads.  fmode: 0 no retention or resets

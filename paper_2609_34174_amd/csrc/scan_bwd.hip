@@ -1139,12 +1139,16 @@ static_assert(lds_bytes_bwd(1, 128, 128, 32, 1) <= 160 * 1024, "bf16 backward ti
 static_assert(lds_bytes_bwd(0, 64, 64, 64, 1) <= 160 * 1024, "fp32 backward tile does not fit LDS");
 static_assert(lds_bytes_bwd(0, 128, 128, 32, 1) <= 160 * 1024, "fp32 backward tile does not fit LDS");
 
-int bwd_wgs_per_cu(int bf16, int d, int m, int C) {
-  const int s = s_shared_fits(bf16, d, m, C, false) ? (bf16 ? 2 : 1) * C * C * (bf16 ? 2 : 4) : 0;
-  int n = 160 * 1024 / (lds_bytes_bwd(bf16, d, m, C, 0) + s);
-  const int waves = cmax(d, m) / 16;
-  if (n * waves > 8) n = 8 / waves;  // two waves per SIMD (register budget)
-  return n < 1 ? 1 : n;
+// Fitted as the forward's (fwd_seg_cost), to the plain call with every output.
+SegCost bwd_seg_cost(int bf16, int d, int m) {
+  const int wide = (d == 128) + (m == 128);
+  static const SegCost bf[3] = {{5.2f, 4.8f, 0.36f, 7.6f, 0.81f, 4.9f, 2, 1.49f},
+                                {2.f, 1.6f, 0.74f, 10.2f, 0.83f, 8.6f, 1, 0.f},
+                                {6.4f, 5.4f, 0.7f, 8.2f, 1.94f, 10.3f, 1, 0.f}};
+  static const SegCost f32[3] = {{2.4f, 1.7f, 1.2f, 9.4f, 0.69f, 15.8f, 1, 0.f},
+                                 {2.f, 2.f, 2.5f, 10.f, 0.9f, 24.f, 1, 0.f},
+                                 {4.f, 4.f, 3.f, 9.f, 1.9f, 42.f, 1, 0.f}};
+  return bf16 ? bf[wide] : f32[wide];
 }
 
 template <class OP, int D, int M, int C, bool ETAV>

@@ -372,17 +372,22 @@ int fwd_chunk_for(int bf16, int d, int m, int requested) {
   return C;
 }
 
-// Workgroups per CU the forward's segmentation aims at: one.  With inputs
-// streamed from HBM, half as many segments of twice the length measured
-// faster at B=8, H=16, T=2048, d=m=64 (main kernel 40 -> 35 us, aggregate
-// pass 19 -> 17 us): fewer concurrent streams, and a quarter less aggregate
-// reading.
-int fwd_wgs_per_cu(int bf16, int d, int m, int C) {
-  (void)bf16;
-  (void)d;
-  (void)m;
-  (void)C;
-  return 1;
+// Fitted to both launches' times over 1 to 256 sequences of 128 to 8000 tokens
+// in every segmentation (bf16: 5-6 % rms; the fp32 and mixed widths from fewer
+// points).  A 64 x 64 workgroup leaves room for a second one on its CU, which
+// costs 0.72 of the first with inputs from the cache, but 1.2 times it from
+// HBM at the sizes that fill the chip (B=4, H=32, T=4096: four segments 246 us
+// a step, two 232 us: fewer concurrent streams); the wider ones run one after
+// the other.
+SegCost fwd_seg_cost(int bf16, int d, int m) {
+  const int wide = (d == 128) + (m == 128);
+  static const SegCost bf[3] = {{1.6f, 4.0f, 0.55f, 1.8f, 0.47f, 1.4f, 2, 2.2f},
+                                {0.f, 4.4f, 0.83f, 3.1f, 0.86f, 2.0f, 1, 0.f},
+                                {0.f, 5.9f, 1.0f, 2.6f, 1.72f, 2.9f, 1, 0.f}};
+  static const SegCost f32[3] = {{2.f, 5.5f, 1.5f, 0.3f, 0.41f, 4.5f, 1, 0.f},
+                                 {2.f, 5.5f, 2.2f, 1.f, 0.9f, 6.8f, 1, 0.f},
+                                 {2.f, 6.f, 3.5f, 4.f, 1.5f, 11.4f, 1, 0.f}};
+  return bf16 ? bf[wide] : f32[wide];
 }
 
 template <class OP, int D, int M, int C, bool ETAV>

@@ -1129,22 +1129,23 @@ int gated_fwd_chunk(int, int, int) { return 64; }
 // the published Lambda: 64-token tiles fit for bf16 64 x 64 maps only.
 int gated_bwd_chunk(int bf16, int d, int m) { return (bf16 && d == 64 && m == 64) ? 64 : 32; }
 
-static constexpr int lds_gated_bwd(int es, int lo, int d, int m, int C) {
-  return es * (C * d + 3 * C * m + lo * C * m + (1 + lo) * 5 * C * C + (1 + lo) * d * m) +
-         4 * (7 * C + 4 * (cmax(d, m) / 16) * C + 40);
-}
-
-int gated_wgs_per_cu(int fwd, int bf16, int d, int m) {
-  const int waves = cmax(d, m) / 16;
-  int n;
-  if (fwd) {
-    const int es = bf16 ? 2 : 4;
-    n = 160 * 1024 / (es * 64 * (d + 2 * m + (bf16 ? m : 0)) + 1024);
-  } else {
-    n = 160 * 1024 / lds_gated_bwd(bf16 ? 2 : 4, bf16 ? 1 : 0, d, m, gated_bwd_chunk(bf16, d, m));
-  }
-  if (n * waves > 8) n = 8 / waves;
-  return n < 1 ? 1 : n;
+// Fitted as the unit-retention scans' (fwd_seg_cost), to the plain gated calls
+// with every output.
+SegCost gated_seg_cost(int fwd, int bf16, int d, int m) {
+  const int wide = (d == 128) + (m == 128);
+  static const SegCost f_bf[3] = {{1.5f, 5.4f, 1.3f, 1.7f, 0.47f, 3.0f, 2, 1.49f},
+                                  {0.f, 6.f, 1.5f, 2.5f, 0.9f, 4.f, 1, 0.f},
+                                  {0.f, 6.8f, 1.8f, 3.3f, 1.9f, 6.7f, 1, 0.f}};
+  static const SegCost f_f32[3] = {{1.f, 5.5f, 2.f, 2.f, 0.5f, 8.f, 1, 0.f},
+                                   {1.f, 5.5f, 3.f, 3.f, 0.9f, 15.f, 1, 0.f},
+                                   {1.f, 6.f, 5.f, 4.f, 1.9f, 29.f, 1, 0.f}};
+  static const SegCost b_bf[3] = {{0.f, 1.4f, 0.1f, 13.8f, 0.57f, 11.3f, 1, 0.f},
+                                  {0.f, 1.4f, 0.5f, 14.f, 0.9f, 21.f, 1, 0.f},
+                                  {0.f, 0.2f, 0.f, 16.7f, 1.4f, 26.6f, 1, 0.f}};
+  static const SegCost b_f32[3] = {{0.f, 1.4f, 0.5f, 14.f, 0.6f, 25.f, 1, 0.f},
+                                   {0.f, 1.4f, 0.5f, 15.f, 0.9f, 42.f, 1, 0.f},
+                                   {0.f, 1.4f, 0.5f, 17.f, 1.4f, 70.f, 1, 0.f}};
+  return (fwd ? (bf16 ? f_bf : f_f32) : (bf16 ? b_bf : b_f32))[wide];
 }
 
 static GArgs gargs(const ScanProblem& p, const GatedPtrs& f) {
