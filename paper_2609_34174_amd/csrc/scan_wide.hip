@@ -203,9 +203,10 @@ struct WScoreArgs {
   const float* cw;
   const int* zc;
   const double* lc;
-  void* Sh;
+  void* Sh;     // scaled scores, or null: not wanted
   void* Sl;
   float* part;  // [KS][BH][Tp][Tp] fp32 partial tiles (KS > 1)
+  float* raw;   // [BH][Tp][Tp] or null: the unscaled contractions Q_t . K_s, fp32
 };
 
 // Tile index within one sequence's lower triangle of 128-token blocks.
@@ -328,8 +329,10 @@ static __global__ void __launch_bounds__(256) wide_score_kernel(const WScoreArgs
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int64_t s = s0 + 16 * i + 4 * q;
-      if (a.KS == 1) score_store<OP, FMODE>(a, bh, t, s, acc[i][j]);
-      else *reinterpret_cast<f32x4*>(a.part + ((ks * a.BH + bh) * a.Tp + t) * a.Tp + s) = acc[i][j];
+      if (a.KS == 1) {
+        if (a.raw) *reinterpret_cast<f32x4*>(a.raw + (bh * a.Tp + t) * a.Tp + s) = acc[i][j];
+        if (a.Sh) score_store<OP, FMODE>(a, bh, t, s, acc[i][j]);
+      } else *reinterpret_cast<f32x4*>(a.part + ((ks * a.BH + bh) * a.Tp + t) * a.Tp + s) = acc[i][j];
     }
   }
 }
@@ -350,7 +353,8 @@ static __global__ void __launch_bounds__(256) wide_score_finish(const WScoreArgs
   const float* p = a.part + (bh * a.Tp + t) * a.Tp + s;
   f32x4 v = *reinterpret_cast<const f32x4*>(p);
   for (int k = 1; k < a.KS; ++k) v += *reinterpret_cast<const f32x4*>(p + k * plane);
-  score_store<OP, FMODE>(a, bh, t, s, v);
+  if (a.raw) *reinterpret_cast<f32x4*>(a.raw + (bh * a.Tp + t) * a.Tp + s) = v;
+  if (a.Sh) score_store<OP, FMODE>(a, bh, t, s, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -366,141 +370,96 @@ static __global__ void __launch_bounds__(256) wide_score_finish(const WScoreArgs
 // ---------------------------------------------------------------------------
 // Gate gradient of the write strengths (Appendix E keeps gate derivatives):
 //   deta_s = -sum_{t>s} F[t][s] (x_s . x_t) (g_s . dY_t).
-// Each lower-triangle 128 x 128 tile contracts dY G^T (over m) and X X^T
-// (over d) into two accumulators, multiplies them with F and the causal mask,
-// and sums its columns over the rows t of each wave's 64-row half; the partial
-// column sums [BH][2 Tp/128][Tp] are added in a fixed order by
-// wide_deta_reduce, which zeroes the tokens a reset overrides.
+// Both contractions come from the score kernels: dY G^T is what the read's
+// scores scale (kept unscaled in the F region, `gy`) and X X^T what the
+// forward's do (its partials, summed here in order).  What is left is a
+// stream over the lower 128 x 128 tiles: the product with F and the causal
+// mask, and column sums over each half of a tile's rows; the partial column
+// sums [BH][2 Tp/128][Tp] are added in a fixed order by wide_colsum_reduce,
+// which zeroes the tokens a reset overrides.  (One workgroup per tile doing
+// both contractions itself took 85 us at B=2, T=1024, 1024 -> 4096: 72
+// workgroups, each 80 steps long; the score kernel's split ranges do X X^T in
+// 14 to 42 us and this stream takes 5 us.)
+// Workgroup: 32 columns of one tile (4 per tile); thread: 4 columns of every
+// 32nd row.
 // ---------------------------------------------------------------------------
 struct WDetaArgs {
-  const void* X;
-  const void* G;
-  const void* dY;
-  int64_t T, Tp, d, m, BH, H;
+  int64_t T, Tp, BH, H;
   const int* zc;
   const double* lc;
   float* dpart;
-  float* deta;
   const uint8_t* reset;
   const float* cw;  // c_s = -eta_s, for Km
-  float* Km;        // [BH][Tp][Tp] or null: K[t][s] = c_s (dY_t . g_s)(x_t . x_s), s < t (lower tiles)
-  float* Fm;        // [BH][Tp][Tp] or null: F[t][s], s < t (lower tiles)
+  const float* gy;  // [BH][Tp][Tp]: dY_t . g_s (lower tiles)
+  const float* xx;  // [KS][BH][Tp][Tp]: partial sums of x_t . x_s (lower tiles)
+  int KS;
+  float* Km;        // [BH][Tp][Tp] or null: K[t][s] = c_s (dY_t . g_s)(x_t . x_s), s < t (may be xx: each element is read first)
+  float* Fm;        // [BH][Tp][Tp] or null: F[t][s], s < t (may be gy, alike)
 };
 
-template <class OP, int FMODE>
+template <int FMODE>
 static __global__ void __launch_bounds__(256) wide_deta_kernel(const WDetaArgs a) {
-  typedef typename OP::elem E;
-  typedef typename OP::frag F;
-  constexpr int BT = 128, BK = 64, NT = 256;
-  __shared__ __attribute__((aligned(16))) E Ps[BT * BK];
-  __shared__ __attribute__((aligned(16))) E Qs[BT * BK];
-  __shared__ float csum[2][BT];
-
+  constexpr int BT = 128;
+  __shared__ __attribute__((aligned(16))) f32x4 part[2][32][8];  // [row half][row lane][column group]
   const int64_t Kp = a.Tp / BT, per_seq = Kp * (Kp + 1) / 2;
-  const int64_t bh = blockIdx.x / per_seq;
+  const int64_t tile = blockIdx.x / 4, quarter = blockIdx.x % 4;
+  const int64_t bh = tile / per_seq;
   int64_t tb, sb;
-  tri_tile(blockIdx.x % per_seq, tb, sb);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wt = w >> 1, ws = w & 1;
-  const int c = lane & 15, q = lane >> 4;
-  const size_t es = sizeof(E);
-
-  f32x4 acc[2][4][4];  // [contraction][s block][t block]: 0: dY_t . g_s, 1: x_t . x_s
-#pragma unroll
-  for (int z = 0; z < 2; ++z)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[z][i][j] = zero4();
-
-#pragma unroll
-  for (int z = 0; z < 2; ++z) {
-    const int64_t w_ = z == 0 ? a.m : a.d;
-    const rsrc_t Qr = make_rsrc(static_cast<const E*>(z == 0 ? a.dY : a.X) + bh * a.T * w_, (uint32_t)(a.T * w_ * es));
-    const rsrc_t Kr = make_rsrc(static_cast<const E*>(z == 0 ? a.G : a.X) + bh * a.T * w_, (uint32_t)(a.T * w_ * es));
-    const uint32_t stride = (uint32_t)(w_ * es);
-    const uint32_t qoff = (uint32_t)(BT * tb * stride), koff = (uint32_t)(BT * sb * stride);
-    GTile<E, BT, BK, NT> qt, kt;
-    qt.load(Qr, qoff, stride, 0, tid);
-    kt.load(Kr, koff, stride, 0, tid);
-    for (int64_t k0 = 0; k0 < w_; k0 += BK) {
-      __syncthreads();
-      qt.store(Qs, tid);
-      kt.store(Ps, tid);
-      __syncthreads();
-      const bool more = k0 + BK < w_;
-      qt.load(Qr, more ? qoff : kOOB, stride, (uint32_t)((k0 + BK) * es), tid);
-      kt.load(Kr, more ? koff : kOOB, stride, (uint32_t)((k0 + BK) * es), tid);
-#pragma unroll
-      for (int kk = 0; kk < BK; kk += 32) {
-        F qf[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) qf[j] = OP::load_n_sep(Qs, BK, 64 * wt + 16 * j, kk, lane);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const F pf = OP::load_n_sep(Ps, BK, 64 * ws + 16 * i, kk, lane);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[z][i][j] = OP::mma(acc[z][i][j], pf, qf[j]);
-        }
-      }
-    }
-  }
-
-  // Lane (c, q) of block (i, j): s = s0 + 16 i + 4 q + r, t = t0 + 16 j + c.
-  const int64_t s0 = BT * sb + 64 * ws, t0 = BT * tb + 64 * wt;
+  tri_tile(tile % per_seq, tb, sb);
+  const int tid = threadIdx.x, cg = tid & 7, rl = tid >> 3;
+  const int64_t s = BT * sb + 32 * quarter + 4 * cg;
   const int* zc = a.zc + bh * a.Tp;
   const double* lc = a.lc + bh * a.Tp;
-  const double ref = FMODE == 2 ? lc[s0 + 63] : 0.0;
-  float col[4][4];  // [i][r]: this lane's partial column sums
+  const size_t plane = (size_t)a.BH * a.Tp * a.Tp;
+  // F is rebased on the log sum at the end of the 64-column block holding s.
+  const double ref = FMODE == 2 ? lc[s | 63] : 0.0;
+  int zs[4] = {0, 0, 0, 0};
+  float bs[4] = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (FMODE >= 1)
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int r = 0; r < 4; ++r) zs[r] = zc[s + r];
+  if constexpr (FMODE == 2)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) col[i][r] = 0.f;
+    for (int r = 0; r < 4; ++r) bs[r] = (float)(ref - lc[s + r]);
+  const f32x4 cv = *reinterpret_cast<const f32x4*>(a.cw + bh * a.Tp + s);
+  f32x4 col[2] = {zero4(), zero4()};
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int64_t t = t0 + 16 * j + c;
+  for (int i = 0; i < 4; ++i) {
+    const int64_t t = BT * tb + 32 * i + rl;
+    const int64_t o = (bh * a.Tp + t) * a.Tp + s;
+    f32x4 x = *reinterpret_cast<const f32x4*>(a.xx + o);
+    for (int k = 1; k < a.KS; ++k) x += *reinterpret_cast<const f32x4*>(a.xx + k * plane + o);
+    const f32x4 y = *reinterpret_cast<const f32x4*>(a.gy + o);
     int zt = 0;
     float at = 0.f;
     if (FMODE >= 1 && t >= 1) zt = zc[t - 1];
     if (FMODE == 2 && t >= 1) at = (float)(lc[t - 1] - ref);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t s = s0 + 16 * i + 4 * q;
-      f32x4 kv, fv;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const bool live = s + r < t && t < a.T;
-        float f = live ? 1.f : 0.f;
-        const int zs = FMODE >= 1 ? zc[s + r] : 0;
-        if (FMODE >= 1 && (zs >> 1) != (zt >> 1)) f = 0.f;
-        if (FMODE == 2 && f != 0.f) f = ((zs ^ zt) & 1 ? -1.f : 1.f) * expf(at + (float)(ref - lc[s + r]));
-        const float k = acc[0][i][j][r] * acc[1][i][j][r];
-        col[i][r] += f * k;
-        fv[r] = f;
-        kv[r] = live ? a.cw[bh * a.Tp + s + r] * k : 0.f;
-      }
-      if (a.Km) {
-        const int64_t o = (bh * a.Tp + t) * a.Tp + s;
-        *reinterpret_cast<f32x4*>(a.Km + o) = kv;
-        *reinterpret_cast<f32x4*>(a.Fm + o) = fv;
-      }
-    }
-  }
-  // Sum over the 16 rows t held by lanes c = 0..15, then write this wave's
-  // 64-row partial for its 64 columns.
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
+    f32x4 kv, fv;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      float v = col[i][r];
-#pragma unroll
-      for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 16);
-      col[i][r] = v;
+      const bool live = s + r < t && t < a.T;
+      float f = live ? 1.f : 0.f;
+      if (FMODE >= 1 && (zs[r] >> 1) != (zt >> 1)) f = 0.f;
+      if (FMODE == 2 && f != 0.f) f = ((zs[r] ^ zt) & 1 ? -1.f : 1.f) * expf(at + bs[r]);
+      const float k = live ? x[r] * y[r] : 0.f;
+      col[i >> 1][r] += f * k;
+      fv[r] = f;
+      kv[r] = cv[r] * k;
     }
-  if (c == 0) {
-    float* out = a.dpart + ((bh * 2 * (a.Tp / BT)) + 2 * tb + wt) * a.Tp;
+    if (a.Km) {
+      *reinterpret_cast<f32x4*>(a.Km + o) = kv;
+      *reinterpret_cast<f32x4*>(a.Fm + o) = fv;
+    }
+  }
+  part[0][rl][cg] = col[0];
+  part[1][rl][cg] = col[1];
+  __syncthreads();
+  if (tid < 16) {
+    const int half = tid >> 3, g = tid & 7;
+    f32x4 v = part[half][0][g];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<f32x4*>(out + s0 + 16 * i + 4 * q) = f32x4{col[i][0], col[i][1], col[i][2], col[i][3]};
+    for (int i = 1; i < 32; ++i) v += part[half][i][g];
+    *reinterpret_cast<f32x4*>(a.dpart + ((bh * 2 * Kp) + 2 * tb + half) * a.Tp + BT * sb + 32 * quarter + 4 * g) = v;
   }
 }
 
@@ -1023,8 +982,11 @@ void wide_gates(const WideProblem& p, const WidePtrs& f, const WideWs& ws, hipSt
 
 // Causal score matrix S[t][s] = F[t][s] c_s (Q_t . K_s) over width w into the
 // score region (lower-triangle 128 x 128 tiles).
+// With `scaled` false only the contractions themselves are formed: into `raw`,
+// or with raw null as the partials of a split contraction alone.
 template <class OP>
-void wide_scores(const WideProblem& p, const WideWs& ws, const void* Q, const void* K, int64_t w, hipStream_t s) {
+void wide_scores(const WideProblem& p, const WideWs& ws, const void* Q, const void* K, int64_t w, bool scaled,
+                 float* raw, hipStream_t s) {
   const int64_t BH = p.B * p.H;
   WScoreArgs sa{};
   sa.Q = Q;
@@ -1036,16 +998,17 @@ void wide_scores(const WideProblem& p, const WideWs& ws, const void* Q, const vo
   sa.cw = ws.cw;
   sa.zc = ws.zc;
   sa.lc = ws.lc;
-  sa.Sh = ws.Sh;
+  sa.Sh = scaled ? ws.Sh : nullptr;
   sa.Sl = OP::kSplit == 2 ? ws.Sl : ws.Sh;
   sa.part = ws.part;
+  sa.raw = raw;
   sa.KS = wide_score_splits(BH, p.Tp, sa.w);
   const int64_t Kp = p.Tp / 128;
   const unsigned tiles = (unsigned)(BH * Kp * (Kp + 1) / 2), sgrid = tiles * sa.KS;
   if (p.fmode == 0) hipLaunchKernelGGL((wide_score_kernel<OP, 0>), dim3(sgrid), dim3(256), 0, s, sa);
   else if (p.fmode == 1) hipLaunchKernelGGL((wide_score_kernel<OP, 1>), dim3(sgrid), dim3(256), 0, s, sa);
   else hipLaunchKernelGGL((wide_score_kernel<OP, 2>), dim3(sgrid), dim3(256), 0, s, sa);
-  if (sa.KS > 1) {
+  if (sa.KS > 1 && (scaled || raw)) {
     if (p.fmode == 0) hipLaunchKernelGGL((wide_score_finish<OP, 0>), dim3(16 * tiles), dim3(256), 0, s, sa);
     else if (p.fmode == 1) hipLaunchKernelGGL((wide_score_finish<OP, 1>), dim3(16 * tiles), dim3(256), 0, s, sa);
     else hipLaunchKernelGGL((wide_score_finish<OP, 2>), dim3(16 * tiles), dim3(256), 0, s, sa);
@@ -1101,13 +1064,13 @@ void wide_prep(const WideProblem& p, const WidePtrs& f, const WideWs& ws, hipStr
 }
 
 // Forward (read = false: Q = K = X, V = G) or transpose read (read = true:
-// Q = dY, K = G, V = X) into `out`.
+// Q = dY, K = G, V = X) into `out`; `raw`, or null, takes the unscaled Q K^T.
 template <class OP>
-hipError_t wide_run(const WideProblem& p, const WidePtrs& f, bool read, float* out, hipStream_t s) {
+hipError_t wide_run(const WideProblem& p, const WidePtrs& f, bool read, float* out, float* raw, hipStream_t s) {
   const WideWs ws = wide_ws(p, f.ws);
   timing_begin(GRADLEV_K_WIDE_SCORE, s);
   wide_prep<OP>(p, f, ws, s);
-  wide_scores<OP>(p, ws, read ? f.dY : f.X, read ? f.G : f.X, read ? p.m : p.d, s);
+  wide_scores<OP>(p, ws, read ? f.dY : f.X, read ? f.G : f.X, read ? p.m : p.d, true, raw, s);
   timing_end(GRADLEV_K_WIDE_SCORE, s);
   timing_begin(GRADLEV_K_WIDE_OUT, s);
   wide_out<OP>(p, f, ws, 0, read, read ? f.dY : f.X, read ? p.m : p.d, read ? f.X : f.G, read ? p.d : p.m, out,
@@ -1119,7 +1082,7 @@ hipError_t wide_run(const WideProblem& p, const WidePtrs& f, bool read, float* o
 }  // namespace
 
 hipError_t launch_wide_fwd(const WideProblem& p, const WidePtrs& f, hipStream_t s) {
-  return p.bf16 ? wide_run<OpBF16>(p, f, false, f.Y, s) : wide_run<OpF32>(p, f, false, f.Y, s);
+  return p.bf16 ? wide_run<OpBF16>(p, f, false, f.Y, nullptr, s) : wide_run<OpF32>(p, f, false, f.Y, nullptr, s);
 }
 
 // The backward of a wide map, each output when requested:
@@ -1132,39 +1095,51 @@ template <class OP>
 static hipError_t wide_bwd(const WideProblem& p, const WidePtrs& f, hipStream_t s) {
   const int64_t BH = p.B * p.H;
   const WideWs ws = wide_ws(p, f.ws);
-  const bool need_gates = f.gtilde || f.dX || f.dG || f.deta || f.dalpha;
+  const bool gates = f.deta || f.dalpha;
+  // The gate gradients' dY G^T, kept unscaled beside the read's scores.
+  float* const gy = gates ? ws.Fm : nullptr;
   if (f.gtilde || f.dX) {
     // The read lands in gtilde, or directly in dX when only dX is requested.
     float* g = f.gtilde ? f.gtilde : f.dX;
-    const hipError_t e = wide_run<OP>(p, f, true, g, s);
+    const hipError_t e = wide_run<OP>(p, f, true, g, gy, s);
     if (e != hipSuccess) return e;
     if (f.dX) {
       timing_begin(GRADLEV_K_WIDE_OUT, s);
       wide_out<OP>(p, f, ws, 1, false, nullptr, 0, f.X, p.d, f.dX, g, s);
       timing_end(GRADLEV_K_WIDE_OUT, s);
     }
-  } else if (need_gates) {
+  } else if (f.dG || gates) {
     wide_gates<OP>(p, f, ws, s);
+    if (gates) {
+      timing_begin(GRADLEV_K_WIDE_SCORE, s);
+      wide_scores<OP>(p, ws, f.dY, f.G, p.m, false, gy, s);
+      timing_end(GRADLEV_K_WIDE_SCORE, s);
+    }
   }
+  const int ks = wide_score_splits(BH, p.Tp, p.d);  // of X X^T
   if (f.dG) {
     timing_begin(GRADLEV_K_WIDE_SCORE, s);
-    wide_scores<OP>(p, ws, f.X, f.X, p.d, s);
+    wide_scores<OP>(p, ws, f.X, f.X, p.d, true, nullptr, s);
     timing_end(GRADLEV_K_WIDE_SCORE, s);
     timing_begin(GRADLEV_K_WIDE_OUT, s);
     wide_out<OP>(p, f, ws, 1, false, nullptr, 0, f.dY, p.m, f.dG, nullptr, s);
     timing_end(GRADLEV_K_WIDE_OUT, s);
   }
-  if (f.deta || f.dalpha) {
-    // The K and F tiles of dalpha take the score region, free from here on.
-    WDetaArgs da{f.X, f.G, f.dY, p.T, p.Tp, p.d, p.m, BH, p.H, ws.zc, ws.lc, ws.dpart, f.deta, f.reset,
-                 ws.cw, f.dalpha ? ws.Km : nullptr, f.dalpha ? ws.Fm : nullptr};
+  if (gates) {
+    timing_begin(GRADLEV_K_WIDE_SCORE, s);
+    // X X^T as the partials of a split contraction (still there after dG's
+    // scores), or whole in the score region, which is free from here on: the
+    // K tiles of dalpha take it too, and its F tiles the place of dY G^T.
+    if (ks == 1) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, ws.Km, s);
+    else if (!f.dG) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, nullptr, s);
+    WDetaArgs da{p.T, p.Tp, BH, p.H, ws.zc, ws.lc, ws.dpart, f.reset, ws.cw, gy, ks == 1 ? ws.Km : ws.part, ks,
+                 f.dalpha ? ws.Km : nullptr, f.dalpha ? ws.Fm : nullptr};
     const int64_t Kp = p.Tp / 128;
     const unsigned grid = (unsigned)(BH * Kp * (Kp + 1) / 2);
     const unsigned rgrid = (unsigned)((BH * p.T + 255) / 256);
-    timing_begin(GRADLEV_K_WIDE_SCORE, s);
-    if (p.fmode == 0) hipLaunchKernelGGL((wide_deta_kernel<OP, 0>), dim3(grid), dim3(256), 0, s, da);
-    else if (p.fmode == 1) hipLaunchKernelGGL((wide_deta_kernel<OP, 1>), dim3(grid), dim3(256), 0, s, da);
-    else hipLaunchKernelGGL((wide_deta_kernel<OP, 2>), dim3(grid), dim3(256), 0, s, da);
+    if (p.fmode == 0) hipLaunchKernelGGL((wide_deta_kernel<0>), dim3(4 * grid), dim3(256), 0, s, da);
+    else if (p.fmode == 1) hipLaunchKernelGGL((wide_deta_kernel<1>), dim3(4 * grid), dim3(256), 0, s, da);
+    else hipLaunchKernelGGL((wide_deta_kernel<2>), dim3(4 * grid), dim3(256), 0, s, da);
     if (f.deta) hipLaunchKernelGGL(wide_colsum_reduce, dim3(rgrid), dim3(256), 0, s, da, f.deta, -1.f);
     if (f.dalpha) {
       if (p.fmode == 0) hipLaunchKernelGGL((wide_dalpha_kernel<0>), dim3(grid), dim3(256), 0, s, da);
