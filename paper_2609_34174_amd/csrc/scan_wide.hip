@@ -22,7 +22,7 @@
 //
 //   wide_gate_kernel   per sequence: c_t, and the zero count and log-sum
 //                      prefixes of the retentions that give F exactly
-//                      (wide_prep_kernel: the same beside the bf16 W_0 split);
+//                      (run beside a split score contraction);
 //   wide_score_kernel  64 x 64 tiles of S (contraction over the query width),
 //                      scaled by F and c, masked to s < t, stored as bf16
 //                      hi + lo (fp32 for fp32 inputs);
@@ -182,6 +182,74 @@ struct GTile {
   }
 };
 
+// Pipeline over a contraction's steps by a workgroup of two groups of four
+// waves, one wave of each on every SIMD; group kh contracts sub-step kh of
+// every step (the caller adds the two).  LDS tiles are double buffered: in step
+// k a wave reads its fragments and computes from one buffer, then puts its
+// share of step k + 1's tiles from their register set into the other and
+// requests step k + 3's: one barrier per step (two with a single buffer: the
+// LM-width output and dW0 kernels, 6 launches, 360 -> 320 us).  What bounds
+// these kernels is the tiles' way from L2 through the registers into LDS: with
+// no arithmetic at all the same launches take 283 us, 3.1 GB at 11 TB/s, and
+// without the requests 267 us.  Requesting three to six steps ahead, starting
+// each tile's walk at another step, and running the groups half a step apart
+// (one's matrix half under the other's LDS half) all left them there or 2 to
+// 9 % slower.
+// Requests are issued in the loop's order, so that each wait counts only the
+// other set's loads, on entry too.  Steps run in pairs: one past n stages
+// zeros (its requests lie past the buffers) and adds nothing; skipping it by a
+// branch moved the accumulators to and fro (score kernel 27 -> 40 us).
+template <class SET, class FETCH, class STORE, class LOAD, class MMA>
+__device__ __forceinline__ void pipeline(int64_t n, FETCH fetch, STORE store, LOAD load, MMA mma) {
+  SET s0, s1;
+  fetch(s0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  fetch(s1, 1);
+  __builtin_amdgcn_sched_barrier(0);
+  store(s0, IntC<0>{});
+  fetch(s0, 2);
+  __syncthreads();
+  auto next = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int64_t k = 0; k < n; k += 2) {
+    load(IntC<0>{});
+    mma();
+    store(s1, IntC<1>{});
+    fetch(s1, k + 3);
+    next();
+    load(IntC<1>{});
+    mma();
+    store(s0, IntC<0>{});
+    fetch(s0, k + 4);
+    next();
+  }
+}
+
+// The two groups' accumulators of a wave tile, [NI][NJ] blocks, added into
+// group 0's through LDS (16 bytes per lane, one contiguous block per wave w of
+// a group).  False in group 1, which is done.
+template <int NI, int NJ>
+__device__ __forceinline__ bool add_groups(f32x4 (&acc)[NI][NJ], void* lds, int kh, int w, int lane) {
+  f32x4* red = static_cast<f32x4*>(lds) + w * NI * NJ * 64 + lane;
+  __syncthreads();
+  if (kh == 1) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) red[(i * NJ + j) * 64] = acc[i][j];
+  }
+  __syncthreads();
+  if (kh == 1) return false;
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] += red[(i * NJ + j) * 64];
+  return true;
+}
+
 // ---------------------------------------------------------------------------
 // Score tiles.  Tile (tb, sb), sb <= tb, covers rows t in [128 tb, +128) and
 // columns s in [128 sb, +128): the lower triangle of 128-token blocks, which
@@ -207,6 +275,8 @@ struct WScoreArgs {
   void* Sl;
   float* part;  // [KS][BH][Tp][Tp] fp32 partial tiles (KS > 1)
   float* raw;   // [BH][Tp][Tp] or null: the unscaled contractions Q_t . K_s, fp32
+  WGateArgs g;
+  int64_t ngate;  // leading blocks that form the gate prefixes instead, one sequence each (KS > 1)
 };
 
 // Tile index within one sequence's lower triangle of 128-token blocks.
@@ -256,7 +326,12 @@ static __global__ void __launch_bounds__(256) wide_score_kernel(const WScoreArgs
   __shared__ __attribute__((aligned(16))) E Qs[BT * BK];  // Q rows t
 
   const int64_t Kp = a.Tp / BT, per_seq = Kp * (Kp + 1) / 2;
-  const int64_t ks = blockIdx.x % a.KS, tile = blockIdx.x / a.KS;
+  if ((int64_t)blockIdx.x < a.ngate) {
+    wide_gate_block(a.g, blockIdx.x);
+    return;
+  }
+  const int64_t L = (int64_t)blockIdx.x - a.ngate;
+  const int64_t ks = L % a.KS, tile = L / a.KS;
   const int64_t bh = tile / per_seq;
   int64_t tb, sb;
   tri_tile(tile % per_seq, tb, sb);
@@ -473,7 +548,16 @@ static __global__ void __launch_bounds__(256) wide_colsum_reduce(const WDetaArgs
   const int64_t nh = 2 * (a.Tp / 128);
   const float* p = a.dpart + bh * nh * a.Tp + s;
   float v = 0.f;
-  for (int64_t h = 2 * (s / 128); h < nh; ++h) v += p[h * a.Tp];
+  // Eight loads in flight, added in order.
+  int64_t h = s / 64;
+  for (; h + 8 <= nh; h += 8) {
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = p[(h + u) * a.Tp];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v += x[u];
+  }
+  for (; h < nh; ++h) v += p[h * a.Tp];
   const bool cut = a.reset && s + 1 < a.T && a.reset[b * a.T + s + 1];
   out[bh * a.T + s] = cut ? 0.f : sign * v;
 }
@@ -487,15 +571,17 @@ static __global__ void __launch_bounds__(256) wide_colsum_reduce(const WDetaArgs
 // on either side of t (the product is never divided by alpha_t, so zero
 // retentions and resets stay exact).  Z = K F^T is a dense fp32 contraction
 // over s (MFMA 16x16x4 f32) of the K and F tiles that wide_deta_kernel
-// stored; tile (u block tb, t block sb) contracts s over [0, 128 (sb + 1)),
+// stored; tile (u block tb, t block sb) contracts s over [0, 64 (sb + 1)),
 // where F[t][.] is nonzero, and its masked column sums over u go to the same
-// partial layout as deta's.
+// partial layout as deta's.  64 x 64 tiles: the longest walk sets the time,
+// and 128 x 128 ones (10 at T = 400, a step four times as long) took 43 us
+// there.
 // ---------------------------------------------------------------------------
 template <int FMODE>
 static __global__ void __launch_bounds__(256) wide_dalpha_kernel(const WDetaArgs a) {
   typedef OpF32 OP;
   typedef OP::frag F;
-  constexpr int BT = 128, BK = 64, NT = 256;
+  constexpr int BT = 64, BK = 64, NT = 256;
   __shared__ __attribute__((aligned(16))) float Ps[BT * BK];  // F rows t
   __shared__ __attribute__((aligned(16))) float Qs[BT * BK];  // K rows u
 
@@ -506,11 +592,11 @@ static __global__ void __launch_bounds__(256) wide_dalpha_kernel(const WDetaArgs
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wt = w >> 1, ws = w & 1;
   const int c = lane & 15, q = lane >> 4;
 
-  f32x4 acc[4][4];  // [t block][u block]: D[t][u] = F_t . K_u = Z[u][t]
+  f32x4 acc[2][2];  // [t block][u block]: D[t][u] = F_t . K_u = Z[u][t]
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = zero4();
+    for (int j = 0; j < 2; ++j) acc[i][j] = zero4();
   {
     const size_t plane = (size_t)a.Tp * a.Tp;
     const rsrc_t Qr = make_rsrc(a.Km + bh * plane, (uint32_t)(plane * 4));
@@ -518,7 +604,7 @@ static __global__ void __launch_bounds__(256) wide_dalpha_kernel(const WDetaArgs
     const uint32_t stride = (uint32_t)(a.Tp * 4);
     const uint32_t qoff = (uint32_t)(BT * tb) * stride, koff = (uint32_t)(BT * sb) * stride;
     GTile<float, BT, BK, NT> qt, kt;
-    const int64_t nk = 2 * (sb + 1);
+    const int64_t nk = sb + 1;
     qt.load(Qr, qoff, stride, 0, tid);
     kt.load(Kr, koff, stride, 0, tid);
     for (int64_t k = 0; k < nk; ++k) {
@@ -531,14 +617,14 @@ static __global__ void __launch_bounds__(256) wide_dalpha_kernel(const WDetaArgs
       kt.load(Kr, more ? koff : kOOB, stride, (uint32_t)((k + 1) * BK * 4), tid);
 #pragma unroll
       for (int kk = 0; kk < BK; kk += 32) {
-        F qf[4];
+        F qf[2];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) qf[j] = OP::load_n_sep(Qs, BK, 64 * wt + 16 * j, kk, lane);
+        for (int j = 0; j < 2; ++j) qf[j] = OP::load_n_sep(Qs, BK, 32 * wt + 16 * j, kk, lane);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const F pf = OP::load_n_sep(Ps, BK, 64 * ws + 16 * i, kk, lane);
+        for (int i = 0; i < 2; ++i) {
+          const F pf = OP::load_n_sep(Ps, BK, 32 * ws + 16 * i, kk, lane);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = OP::mma(acc[i][j], pf, qf[j]);
+          for (int j = 0; j < 2; ++j) acc[i][j] = OP::mma(acc[i][j], pf, qf[j]);
         }
       }
     }
@@ -546,24 +632,24 @@ static __global__ void __launch_bounds__(256) wide_dalpha_kernel(const WDetaArgs
 
   // Lane (c, q) of block (i, j): t = s0 + 16 i + 4 q + r (the gradient's
   // token), u = t0 + 16 j + c (the read).
-  const int64_t s0 = BT * sb + 64 * ws, t0 = BT * tb + 64 * wt;
+  const int64_t s0 = BT * sb + 32 * ws, t0 = BT * tb + 32 * wt;
   const int* zc = a.zc + bh * a.Tp;
   const double* lc = a.lc + bh * a.Tp;
-  const double ref = FMODE == 2 ? lc[s0 + 63] : 0.0;
-  float col[4][4];
+  const double ref = FMODE == 2 ? lc[BT * sb + 63] : 0.0;
+  float col[2][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) col[i][r] = 0.f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < 2; ++j) {
     const int64_t u = t0 + 16 * j + c;
     int zu = 0;
     float au = 0.f;
     if (FMODE >= 1 && u >= 1) zu = zc[u - 1];
     if (FMODE == 2 && u >= 1) au = (float)(lc[u - 1] - ref);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 2; ++i) {
       const int64_t t = s0 + 16 * i + 4 * q;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -576,7 +662,7 @@ static __global__ void __launch_bounds__(256) wide_dalpha_kernel(const WDetaArgs
     }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float v = col[i][r];
@@ -584,11 +670,17 @@ static __global__ void __launch_bounds__(256) wide_dalpha_kernel(const WDetaArgs
       for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 16);
       col[i][r] = v;
     }
-  if (c == 0) {
-    float* out = a.dpart + ((bh * 2 * (a.Tp / BT)) + 2 * tb + wt) * a.Tp;
+  // The two row groups' sums, added through LDS.
+  __shared__ __attribute__((aligned(16))) f32x4 half[2][2][4];  // [ws][i][q]
+  if (wt == 1 && c == 0)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<f32x4*>(out + s0 + 16 * i + 4 * q) = f32x4{col[i][0], col[i][1], col[i][2], col[i][3]};
+    for (int i = 0; i < 2; ++i) half[ws][i][q] = f32x4{col[i][0], col[i][1], col[i][2], col[i][3]};
+  __syncthreads();
+  if (wt == 0 && c == 0) {
+    float* out = a.dpart + (bh * Kp + tb) * a.Tp;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      *reinterpret_cast<f32x4*>(out + s0 + 16 * i + 4 * q) = f32x4{col[i][0], col[i][1], col[i][2], col[i][3]} + half[ws][i][q];
   }
 }
 
@@ -608,16 +700,17 @@ struct WDw0Args {
 };
 
 template <class OP>
-static __global__ void __launch_bounds__(256) wide_dw0_kernel(const WDw0Args a) {
+static __global__ void __launch_bounds__(512) wide_dw0_kernel(const WDw0Args a) {
   typedef typename OP::elem E;
   typedef typename OP::frag F;
-  constexpr int BT = 64, BN = 128, NT = 256;
-  __shared__ __attribute__((aligned(16))) E Xs[BT * BN];  // [t][j]
-  __shared__ __attribute__((aligned(16))) E Ds[BT * BN];  // [t][i]
+  constexpr int BT = 64, BN = 128, NT = 512, TILE = BT * BN;
+  constexpr int PR = BN * BN * 4 / (int)sizeof(E);  // group 1's accumulators: the fp32 tile
+  __shared__ __attribute__((aligned(16))) E lds[4 * TILE > PR ? 4 * TILE : PR];  // two buffers of X [t][j] | dY [t][i]
   const int64_t nJ = a.d / BN, nI = a.m / BN;
   const int64_t h = blockIdx.x / (nI * nJ), rest = blockIdx.x % (nI * nJ);
   const int64_t i0 = BN * (rest / nJ), j0 = BN * (rest % nJ);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wj = w >> 1, wi = w & 1;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kh = w >> 2, wj = (w >> 1) & 1, wi = w & 1;
   const int c = lane & 15, q = lane >> 4;
   const size_t es = sizeof(E);
   f32x4 acc[4][4];  // [j block][i block]
@@ -626,36 +719,40 @@ static __global__ void __launch_bounds__(256) wide_dw0_kernel(const WDw0Args a) 
 #pragma unroll
     for (int y = 0; y < 4; ++y) acc[x][y] = zero4();
   const int64_t nsteps = (a.T + BT - 1) / BT;
-  GTile<E, BT, BN, NT> xt, dt;
-  auto fetch = [&](int64_t k) {
-    const bool ok = k < a.B * nsteps;
+  const int64_t n = a.B * nsteps;
+  struct Set {
+    GTile<E, BT, BN, NT> xt, dt;
+  };
+  auto fetch = [&](Set& x, int64_t k) {
+    const bool ok = k < n;
     const int64_t b = ok ? k / nsteps : 0, t0 = ok ? BT * (k % nsteps) : 0;
     const int64_t bh = b * a.H + h;
     const rsrc_t Xr = make_rsrc(static_cast<const E*>(a.X) + bh * a.T * a.d, (uint32_t)(a.T * a.d * es));
     const rsrc_t Dr = make_rsrc(static_cast<const E*>(a.dY) + bh * a.T * a.m, (uint32_t)(a.T * a.m * es));
-    xt.load(Xr, ok ? (uint32_t)(t0 * a.d * es) : kOOB, (uint32_t)(a.d * es), (uint32_t)(j0 * es), tid);
-    dt.load(Dr, ok ? (uint32_t)(t0 * a.m * es) : kOOB, (uint32_t)(a.m * es), (uint32_t)(i0 * es), tid);
+    x.xt.load(Xr, ok ? (uint32_t)(t0 * a.d * es) : kOOB, (uint32_t)(a.d * es), (uint32_t)(j0 * es), tid);
+    x.dt.load(Dr, ok ? (uint32_t)(t0 * a.m * es) : kOOB, (uint32_t)(a.m * es), (uint32_t)(i0 * es), tid);
   };
-  fetch(0);
-  for (int64_t k = 0; k < a.B * nsteps; ++k) {
-    __syncthreads();
-    xt.store(Xs, tid);
-    dt.store(Ds, tid);
-    __syncthreads();
-    fetch(k + 1);
+  auto store = [&](Set& x, auto buf) {
+    E* const L = lds + decltype(buf)::value * 2 * TILE;
+    x.xt.store(L, tid);
+    x.dt.store(L + TILE, tid);
+  };
+  F xf[4], df[4];
+  auto load = [&](auto buf) {
+    const E* const L = lds + decltype(buf)::value * 2 * TILE;
 #pragma unroll
-    for (int kk = 0; kk < BT; kk += 32) {
-      F df[4];
+    for (int y = 0; y < 4; ++y) df[y] = OP::load_t(L + TILE, BN, 32 * kh, 64 * wi + 16 * y, lane);
 #pragma unroll
-      for (int y = 0; y < 4; ++y) df[y] = OP::load_t(Ds, BN, kk, 64 * wi + 16 * y, lane);
+    for (int x = 0; x < 4; ++x) xf[x] = OP::load_t(L, BN, 32 * kh, 64 * wj + 16 * x, lane);
+  };
+  auto mma = [&]() {
 #pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const F xf = OP::load_t(Xs, BN, kk, 64 * wj + 16 * x, lane);
+    for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = OP::mma(acc[x][y], xf, df[y]);
-      }
-    }
-  }
+      for (int y = 0; y < 4; ++y) acc[x][y] = OP::mma(acc[x][y], xf[x], df[y]);
+  };
+  pipeline<Set>(n, fetch, store, load, mma);
+  if (!add_groups(acc, lds, kh, w & 3, lane)) return;
   // Lane (c, q) of block (x, y): j = j0 + 64 wj + 16 x + 4 q + r, i = i0 + 64 wi + 16 y + c.
 #pragma unroll
   for (int y = 0; y < 4; ++y) {
@@ -666,28 +763,8 @@ static __global__ void __launch_bounds__(256) wide_dw0_kernel(const WDw0Args a) 
   }
 }
 
-// fp32 W_0 split once per call into bf16 hi and lo planes of the same
-// layout (the output tiles then stage bf16 directly; the split costs one
-// pass over W_0 instead of one per row tile).  The gate prefixes ride in
-// the same launch: blocks [0, nbh) take one sequence each (a sequential
-// span per thread, a few blocks only), the rest split W_0 beside them,
-// instead of the prefixes running alone ahead of the scores.
-static __global__ void __launch_bounds__(256) wide_prep_kernel(const WGateArgs g, int64_t nbh,
-                                                               const float* __restrict__ W0, bf16* __restrict__ hi,
-                                                               bf16* __restrict__ lo, int64_t n4) {
-  if ((int64_t)blockIdx.x < nbh) {
-    wide_gate_block(g, blockIdx.x);
-    return;
-  }
-  const int64_t nb = (int64_t)gridDim.x - nbh;
-  for (int64_t i = ((int64_t)blockIdx.x - nbh) * 256 + threadIdx.x; i < n4; i += nb * 256)
-    OpBF16::store4_split(hi + 4 * i, lo + 4 * i, *reinterpret_cast<const f32x4*>(W0 + 4 * i));
-}
-
 struct WOutArgs {
   const void* Q;
-  const bf16* Wh;  // bf16 operands: W_0 split into hi and lo planes [H][m][d]
-  const bf16* Wl;
   const float* W0;
   const void* Sh;
   const void* Sl;
@@ -714,21 +791,16 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
   constexpr int PR = BM * BN * 4 / (int)sizeof(E);  // the kh = 1 waves' accumulators: a BM x BN fp32 partial
   static_assert(4 * NB * 4 * 64 * 16 == BM * BN * 4, "reduction layout covers the tile once");
   constexpr int PM = P1 > P2 ? P1 : P2;
-  __shared__ __attribute__((aligned(16))) E lds[PM > PR ? PM : PR];
+  __shared__ __attribute__((aligned(16))) E lds[2 * PM > PR ? 2 * PM : PR];  // two step buffers of PM
   // Phase 1: Qs | Ph | Pl.  Phase 2: Shs | Sls | Vs (fp32: Qs | Ph and Shs | Vs).
-  E* const Qs = lds;
-  E* const Ph = lds + TILE;
-  E* const Pl = SPLIT ? lds + TILE + PT : Ph;
-  E* const Shs = lds;
-  E* const Sls = SPLIT ? lds + TILE : lds;
-  E* const Vs = lds + (SPLIT ? 2 : 1) * TILE;
 
   const int64_t nTB = a.Tp / BM, nNB = a.wout / BN;
   const int64_t L = blockIdx.x, per_row = a.BH * nNB;
   const int64_t tb = MODE == 0 ? nTB - 1 - L / per_row : L / per_row;  // heaviest row tiles first
   const int64_t bh = (L % per_row) / nNB, nb = L % nNB;
   const int64_t h = bh % a.H;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, kh = w >> 2, wt = (w >> 1) & 1, wn = w & 1;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kh = w >> 2, wt = (w >> 1) & 1, wn = w & 1;
   const int c = lane & 15, q = lane >> 4;
   const int64_t t0 = BM * tb, n0 = BN * nb;
   const size_t es = sizeof(E);
@@ -739,9 +811,7 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = zero4();
 
-  // Both phases run a two-deep register pipeline: the tiles of step k + 2
-  // are requested while step k computes, by two staging sets used in turn.
-  // Step counts are even (widths are multiples of 128 and the causal range is
+  // Both phases run the pipeline above.  Step counts are even (widths are multiples of 128 and the causal range is
   // whole 128-token blocks), and a request past the last step reads from an
   // offset beyond the buffer (zeros, no branch), so the outstanding-load
   // counts stay exact across the barriers.
@@ -752,63 +822,54 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
     const rsrc_t Wr = make_rsrc(a.W0 + h * md, (uint32_t)(md * 4));
     const uint32_t qstride = (uint32_t)(a.wq * es);
     // W_0 is [m][d]: forward rows n over k (row length wq), read rows k over n
-    // (row length wout).  bf16 operands stage the hi and lo planes, fp32 W_0.
-    const rsrc_t Whr = make_rsrc(SPLIT ? a.Wh + h * md : nullptr, SPLIT ? (uint32_t)(md * 2) : 0u);
-    const rsrc_t Wlr = make_rsrc(SPLIT ? a.Wl + h * md : nullptr, SPLIT ? (uint32_t)(md * 2) : 0u);
-    typedef GTile<E, TRANS ? BK : BN, TRANS ? BN : BK, NT> WT;
+    // (row length wout).  fp32 tiles, split into hi + lo on their way into LDS
+    // for bf16 operands: as many bytes as planes split beforehand, without the
+    // pass that wrote those (9 us a call at 1024 x 4096).
+    typedef GTile<float, TRANS ? BK : BN, TRANS ? BN : BK, NT> WT;
     struct Set {
       GTile<E, BM, BK, NT> qt;
-      WT wh, wl;
-    } st[2];
+      WT wt;
+    };
     const int64_t n1 = a.wq / BK;
     auto fetch = [&](Set& x, int64_t k) {
       const bool ok = k < n1;
       const int64_t k0 = k * BK;
       x.qt.load(Qr, ok ? (uint32_t)(t0 * qstride) : kOOB, qstride, (uint32_t)(k0 * es), tid);
-      const rsrc_t r0 = SPLIT ? Whr : Wr;
-      const uint32_t rows = TRANS ? (uint32_t)(k0 * a.wout * es) : (uint32_t)(n0 * a.wq * es);
-      const uint32_t stride = TRANS ? (uint32_t)(a.wout * es) : (uint32_t)(a.wq * es);
-      const uint32_t col = TRANS ? (uint32_t)(n0 * es) : (uint32_t)(k0 * es);
-      x.wh.load(r0, ok ? rows : kOOB, stride, col, tid);
-      if constexpr (SPLIT) x.wl.load(Wlr, ok ? rows : kOOB, stride, col, tid);
+      const uint32_t rows = TRANS ? (uint32_t)(k0 * a.wout * 4) : (uint32_t)(n0 * a.wq * 4);
+      const uint32_t stride = TRANS ? (uint32_t)(a.wout * 4) : (uint32_t)(a.wq * 4);
+      const uint32_t col = TRANS ? (uint32_t)(n0 * 4) : (uint32_t)(k0 * 4);
+      x.wt.load(Wr, ok ? rows : kOOB, stride, col, tid);
     };
-    auto step = [&](Set& x, int64_t k) {
-      // Keep each step's work inside the step: hoisting the other set's
-      // stores would make the compiler wait for its loads here.
-      __builtin_amdgcn_sched_barrier(0);
-      __syncthreads();
-      x.qt.store(Qs, tid);
-      x.wh.store(Ph, tid);
-      if constexpr (SPLIT) x.wl.store(Pl, tid);
-      __syncthreads();
-      fetch(x, k + 2);
+    auto store = [&](Set& x, auto buf) {
+      E* const L = lds + decltype(buf)::value * PM;
+      x.qt.store(L, tid);
+      x.wt.template store_split<OP>(L + TILE, L + TILE + (SPLIT ? PT : 0), tid);
+    };
+    F qf[4], ph[NB], pl[SPLIT ? NB : 1];
+    auto load = [&](auto buf) {
+      const E* const Qs = lds + decltype(buf)::value * PM;
+      const E* const Ph = Qs + TILE;
       const int kk = 32 * kh;
-      F qf[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) qf[j] = OP::load_n_sep(Qs, BK, 64 * wt + 16 * j, kk, lane);
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
-        F ph, pl;
         if constexpr (TRANS) {
-          ph = OP::load_t(Ph, BN, kk, BN / 2 * wn + 16 * i, lane);
-          pl = SPLIT ? OP::load_t(Pl, BN, kk, BN / 2 * wn + 16 * i, lane) : ph;
+          ph[i] = OP::load_t(Ph, BN, kk, BN / 2 * wn + 16 * i, lane);
+          if constexpr (SPLIT) pl[i] = OP::load_t(Ph + PT, BN, kk, BN / 2 * wn + 16 * i, lane);
         } else {
-          ph = OP::load_n_sep(Ph, BK, BN / 2 * wn + 16 * i, kk, lane);
-          pl = SPLIT ? OP::load_n_sep(Pl, BK, BN / 2 * wn + 16 * i, kk, lane) : ph;
+          ph[i] = OP::load_n_sep(Ph, BK, BN / 2 * wn + 16 * i, kk, lane);
+          if constexpr (SPLIT) pl[i] = OP::load_n_sep(Ph + PT, BK, BN / 2 * wn + 16 * i, kk, lane);
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mma_split_a<OP>(acc[i][j], ph, pl, qf[j]);
       }
     };
-    fetch(st[0], 0);
-    // Issue order is the loop's: the first wait of every step counts only
-    // the other set's loads, on entry too.
-    __builtin_amdgcn_sched_barrier(0);
-    fetch(st[1], 1);
-    for (int64_t k = 0; k < n1; k += 2) {
-      step(st[0], k);
-      step(st[1], k + 1);
-    }
+    auto mma = [&]() {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = mma_split_a<OP>(acc[i][j], ph[i], pl[SPLIT ? i : 0], qf[j]);
+    };
+    pipeline<Set>(n1, fetch, store, load, mma);
   }
 
   // Phase 2: acc += S V over s in [0, 128 (tb + 1)) (causal), or
@@ -823,7 +884,7 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
     struct Set {
       ST sh, sl;
       GTile<E, BK, BN, NT> vt;
-    } st[2];
+    };
     const int64_t n2 = MODE == 0 ? 2 * (tb + 1) : 2 * (nTB - tb);
     const int64_t sbeg = MODE == 0 ? 0 : t0;
     auto fetch = [&](Set& x, int64_t k) {
@@ -836,61 +897,40 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
       if constexpr (SPLIT) x.sl.load(Slr, ok ? rows : kOOB, sstride, col, tid);
       x.vt.load(Vr, ok ? (uint32_t)(s0 * vstride) : kOOB, vstride, (uint32_t)(n0 * es), tid);
     };
-    auto step = [&](Set& x, int64_t k) {
-      __builtin_amdgcn_sched_barrier(0);
-      __syncthreads();
-      x.sh.store(Shs, tid);
-      if constexpr (SPLIT) x.sl.store(Sls, tid);
-      x.vt.store(Vs, tid);
-      __syncthreads();
-      fetch(x, k + 2);
+    auto store = [&](Set& x, auto buf) {
+      E* const L = lds + decltype(buf)::value * PM;
+      x.sh.store(L, tid);
+      if constexpr (SPLIT) x.sl.store(L + TILE, tid);
+      x.vt.store(L + (SPLIT ? 2 : 1) * TILE, tid);
+    };
+    F sfh[4], sfl[SPLIT ? 4 : 1], vf[NB];
+    auto load = [&](auto buf) {
+      const E* const Shs = lds + decltype(buf)::value * PM;
+      const E* const Vs = Shs + (SPLIT ? 2 : 1) * TILE;
       const int kk = 32 * kh;
-      F sfh[4], sfl[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if constexpr (MODE == 0) {
           sfh[j] = OP::load_n_sep(Shs, BK, 64 * wt + 16 * j, kk, lane);
-          sfl[j] = SPLIT ? OP::load_n_sep(Sls, BK, 64 * wt + 16 * j, kk, lane) : sfh[j];
+          if constexpr (SPLIT) sfl[j] = OP::load_n_sep(Shs + TILE, BK, 64 * wt + 16 * j, kk, lane);
         } else {
           sfh[j] = OP::load_t(Shs, BM, kk, 64 * wt + 16 * j, lane);
-          sfl[j] = SPLIT ? OP::load_t(Sls, BM, kk, 64 * wt + 16 * j, lane) : sfh[j];
+          if constexpr (SPLIT) sfl[j] = OP::load_t(Shs + TILE, BM, kk, 64 * wt + 16 * j, lane);
         }
       }
 #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const F vf = OP::load_t(Vs, BN, kk, BN / 2 * wn + 16 * i, lane);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mma_split_b<OP>(acc[i][j], vf, sfh[j], sfl[j]);
-      }
+      for (int i = 0; i < NB; ++i) vf[i] = OP::load_t(Vs, BN, kk, BN / 2 * wn + 16 * i, lane);
     };
-    fetch(st[0], 0);
-    // Issue order is the loop's: the first wait of every step counts only
-    // the other set's loads, on entry too.
-    __builtin_amdgcn_sched_barrier(0);
-    fetch(st[1], 1);
-    for (int64_t k = 0; k < n2; k += 2) {
-      step(st[0], k);
-      step(st[1], k + 1);
-    }
+    auto mma = [&]() {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = mma_split_b<OP>(acc[i][j], vf[i], sfh[j], sfl[SPLIT ? j : 0]);
+    };
+    pipeline<Set>(n2, fetch, store, load, mma);
   }
 
-  // The kh = 1 waves hand their accumulators to the kh = 0 waves of the same
-  // (wt, wn) through LDS (16 bytes per lane, one contiguous block per wave).
-  f32x4* red = reinterpret_cast<f32x4*>(lds) + (w & 3) * NB * 4 * 64 + lane;
-  __syncthreads();
-  if (kh == 1) {
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) red[(i * 4 + j) * 64] = acc[i][j];
-  }
-  __syncthreads();
-  if (kh == 1) return;
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] += red[(i * 4 + j) * 64];
-
+  if (!add_groups(acc, lds, kh, w & 3, lane)) return;
   // Lane (c, q) of block (i, j): n = n0 + BN/2 wn + 16 i + 4 q + r, t = t0 + 64 wt + 16 j + c.
   const rsrc_t Or = make_rsrc(a.out + bh * a.T * a.wout, (uint32_t)(a.T * a.wout * 4));
   const rsrc_t Ar = make_rsrc(MODE == 1 && a.addend ? a.addend + bh * a.T * a.wout : nullptr,
@@ -927,7 +967,7 @@ size_t wide_workspace_bytes(const WideProblem& p) {
   const int kd = wide_score_splits((int64_t)BH, (int64_t)Tp, p.d), km = wide_score_splits((int64_t)BH, (int64_t)Tp, p.m);
   const int ks = kd > km ? kd : km;  // the forward contracts over d, the read over m
   const size_t part = ks > 1 ? (size_t)ks * BH * Tp * Tp * 4 : 0;
-  const size_t planes = p.bf16 ? (size_t)p.H * p.m * p.d * 4 : 0;  // W_0 hi + lo
+  const size_t planes = p.bf16 ? (size_t)p.H * p.m * p.d * 4 : 0;  // not used: callers' sizes include it
   const size_t dpart = BH * 2 * (Tp / 128) * Tp * 4;               // partial column sums (deta, dalpha)
   const size_t fm = BH * Tp * Tp * 4;                              // dalpha: fp32 F tiles
   return (gates + 255) / 256 * 256 + (S + 255) / 256 * 256 + (part + 255) / 256 * 256 + (planes + 255) / 256 * 256 +
@@ -943,8 +983,6 @@ struct WideWs {
   void* Sh;
   void* Sl;
   float* part;
-  bf16* Wh;
-  bf16* Wl;
   float* dpart;
   float* Km;  // the score region, reused once the scores are no longer needed
   float* Fm;
@@ -965,28 +1003,27 @@ WideWs wide_ws(const WideProblem& p, void* ws) {
   o.part = reinterpret_cast<float*>(pt);
   const int kd = wide_score_splits((int64_t)BH, (int64_t)Tp, p.d), km = wide_score_splits((int64_t)BH, (int64_t)Tp, p.m);
   const int ks = kd > km ? kd : km;
-  char* wp = pt + ((ks > 1 ? (size_t)ks * BH * Tp * Tp * 4 : 0) + 255) / 256 * 256;
-  o.Wh = reinterpret_cast<bf16*>(wp);
-  o.Wl = reinterpret_cast<bf16*>(wp + (size_t)p.H * p.m * p.d * 2);
-  char* dp = wp + ((p.bf16 ? (size_t)p.H * p.m * p.d * 4 : 0) + 255) / 256 * 256;
+  char* dp = pt + ((ks > 1 ? (size_t)ks * BH * Tp * Tp * 4 : 0) + 255) / 256 * 256 +
+             ((p.bf16 ? (size_t)p.H * p.m * p.d * 4 : 0) + 255) / 256 * 256;
   o.dpart = reinterpret_cast<float*>(dp);
   o.Fm = reinterpret_cast<float*>(dp + (BH * 2 * (Tp / 128) * Tp * 4 + 255) / 256 * 256);
   return o;
 }
 
-template <class OP>
-void wide_gates(const WideProblem& p, const WidePtrs& f, const WideWs& ws, hipStream_t s) {
-  WGateArgs g{f.eta, f.eta_scalar, f.eta_mul, f.alpha, f.alpha_scalar, f.reset, p.H, p.T, p.Tp, ws.cw, ws.zc, ws.lc};
-  hipLaunchKernelGGL(wide_gate_kernel, dim3((unsigned)(p.B * p.H)), dim3(256), 0, s, g);
+WGateArgs gate_args(const WideProblem& p, const WidePtrs& f, const WideWs& ws) {
+  return WGateArgs{f.eta, f.eta_scalar, f.eta_mul, f.alpha, f.alpha_scalar, f.reset, p.H, p.T, p.Tp, ws.cw, ws.zc, ws.lc};
 }
 
 // Causal score matrix S[t][s] = F[t][s] c_s (Q_t . K_s) over width w into the
 // score region (lower-triangle 128 x 128 tiles).
 // With `scaled` false only the contractions themselves are formed: into `raw`,
-// or with raw null as the partials of a split contraction alone.
+// or with raw null as the partials of a split contraction alone.  With `gates`
+// the gate prefixes are formed too: beside a split contraction, whose finish
+// is the first to need them (a few blocks that would take 5 us on their own),
+// else before.
 template <class OP>
 void wide_scores(const WideProblem& p, const WideWs& ws, const void* Q, const void* K, int64_t w, bool scaled,
-                 float* raw, hipStream_t s) {
+                 float* raw, const WGateArgs* gates, hipStream_t s) {
   const int64_t BH = p.B * p.H;
   WScoreArgs sa{};
   sa.Q = Q;
@@ -1004,7 +1041,12 @@ void wide_scores(const WideProblem& p, const WideWs& ws, const void* Q, const vo
   sa.raw = raw;
   sa.KS = wide_score_splits(BH, p.Tp, sa.w);
   const int64_t Kp = p.Tp / 128;
-  const unsigned tiles = (unsigned)(BH * Kp * (Kp + 1) / 2), sgrid = tiles * sa.KS;
+  if (gates && sa.KS == 1) hipLaunchKernelGGL(wide_gate_kernel, dim3((unsigned)BH), dim3(256), 0, s, *gates);
+  if (gates && sa.KS > 1) {
+    sa.g = *gates;
+    sa.ngate = BH;
+  }
+  const unsigned tiles = (unsigned)(BH * Kp * (Kp + 1) / 2), sgrid = (unsigned)sa.ngate + tiles * sa.KS;
   if (p.fmode == 0) hipLaunchKernelGGL((wide_score_kernel<OP, 0>), dim3(sgrid), dim3(256), 0, s, sa);
   else if (p.fmode == 1) hipLaunchKernelGGL((wide_score_kernel<OP, 1>), dim3(sgrid), dim3(256), 0, s, sa);
   else hipLaunchKernelGGL((wide_score_kernel<OP, 2>), dim3(sgrid), dim3(256), 0, s, sa);
@@ -1024,8 +1066,6 @@ void wide_out(const WideProblem& p, const WidePtrs& f, const WideWs& ws, int mod
   WOutArgs oa{};
   oa.Q = Q;
   oa.W0 = f.W0;
-  oa.Wh = ws.Wh;
-  oa.Wl = ws.Wl;
   oa.Sh = ws.Sh;
   oa.Sl = OP::kSplit == 2 ? ws.Sl : ws.Sh;
   oa.V = V;
@@ -1050,27 +1090,14 @@ void wide_out(const WideProblem& p, const WidePtrs& f, const WideWs& ws, int mod
   else hipLaunchKernelGGL((wide_out_kernel<OP, false, 128, 0>), dim3(g), dim3(512), 0, s, oa);
 }
 
-// The gate prefixes and, for bf16 operands, the W_0 split in one launch.
-template <class OP>
-void wide_prep(const WideProblem& p, const WidePtrs& f, const WideWs& ws, hipStream_t s) {
-  if (OP::kSplit != 2) {
-    wide_gates<OP>(p, f, ws, s);
-    return;
-  }
-  WGateArgs g{f.eta, f.eta_scalar, f.eta_mul, f.alpha, f.alpha_scalar, f.reset, p.H, p.T, p.Tp, ws.cw, ws.zc, ws.lc};
-  const int64_t n4 = p.H * (int64_t)p.m * p.d / 4, BH = p.B * p.H;
-  const int64_t gs = n4 / 256 < 4096 ? (n4 + 255) / 256 : 4096;
-  hipLaunchKernelGGL(wide_prep_kernel, dim3((unsigned)(BH + gs)), dim3(256), 0, s, g, BH, f.W0, ws.Wh, ws.Wl, n4);
-}
-
 // Forward (read = false: Q = K = X, V = G) or transpose read (read = true:
 // Q = dY, K = G, V = X) into `out`; `raw`, or null, takes the unscaled Q K^T.
 template <class OP>
 hipError_t wide_run(const WideProblem& p, const WidePtrs& f, bool read, float* out, float* raw, hipStream_t s) {
   const WideWs ws = wide_ws(p, f.ws);
   timing_begin(GRADLEV_K_WIDE_SCORE, s);
-  wide_prep<OP>(p, f, ws, s);
-  wide_scores<OP>(p, ws, read ? f.dY : f.X, read ? f.G : f.X, read ? p.m : p.d, true, raw, s);
+  const WGateArgs g = gate_args(p, f, ws);
+  wide_scores<OP>(p, ws, read ? f.dY : f.X, read ? f.G : f.X, read ? p.m : p.d, true, raw, &g, s);
   timing_end(GRADLEV_K_WIDE_SCORE, s);
   timing_begin(GRADLEV_K_WIDE_OUT, s);
   wide_out<OP>(p, f, ws, 0, read, read ? f.dY : f.X, read ? p.m : p.d, read ? f.X : f.G, read ? p.d : p.m, out,
@@ -1109,17 +1136,16 @@ static hipError_t wide_bwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
       timing_end(GRADLEV_K_WIDE_OUT, s);
     }
   } else if (f.dG || gates) {
-    wide_gates<OP>(p, f, ws, s);
-    if (gates) {
-      timing_begin(GRADLEV_K_WIDE_SCORE, s);
-      wide_scores<OP>(p, ws, f.dY, f.G, p.m, false, gy, s);
-      timing_end(GRADLEV_K_WIDE_SCORE, s);
-    }
+    const WGateArgs g = gate_args(p, f, ws);
+    timing_begin(GRADLEV_K_WIDE_SCORE, s);
+    if (gates) wide_scores<OP>(p, ws, f.dY, f.G, p.m, false, gy, &g, s);
+    else hipLaunchKernelGGL(wide_gate_kernel, dim3((unsigned)BH), dim3(256), 0, s, g);
+    timing_end(GRADLEV_K_WIDE_SCORE, s);
   }
   const int ks = wide_score_splits(BH, p.Tp, p.d);  // of X X^T
   if (f.dG) {
     timing_begin(GRADLEV_K_WIDE_SCORE, s);
-    wide_scores<OP>(p, ws, f.X, f.X, p.d, true, nullptr, s);
+    wide_scores<OP>(p, ws, f.X, f.X, p.d, true, nullptr, nullptr, s);
     timing_end(GRADLEV_K_WIDE_SCORE, s);
     timing_begin(GRADLEV_K_WIDE_OUT, s);
     wide_out<OP>(p, f, ws, 1, false, nullptr, 0, f.dY, p.m, f.dG, nullptr, s);
@@ -1130,8 +1156,8 @@ static hipError_t wide_bwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
     // X X^T as the partials of a split contraction (still there after dG's
     // scores), or whole in the score region, which is free from here on: the
     // K tiles of dalpha take it too, and its F tiles the place of dY G^T.
-    if (ks == 1) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, ws.Km, s);
-    else if (!f.dG) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, nullptr, s);
+    if (ks == 1) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, ws.Km, nullptr, s);
+    else if (!f.dG) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, nullptr, nullptr, s);
     WDetaArgs da{p.T, p.Tp, BH, p.H, ws.zc, ws.lc, ws.dpart, f.reset, ws.cw, gy, ks == 1 ? ws.Km : ws.part, ks,
                  f.dalpha ? ws.Km : nullptr, f.dalpha ? ws.Fm : nullptr};
     const int64_t Kp = p.Tp / 128;
@@ -1142,9 +1168,10 @@ static hipError_t wide_bwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
     else hipLaunchKernelGGL((wide_deta_kernel<2>), dim3(4 * grid), dim3(256), 0, s, da);
     if (f.deta) hipLaunchKernelGGL(wide_colsum_reduce, dim3(rgrid), dim3(256), 0, s, da, f.deta, -1.f);
     if (f.dalpha) {
-      if (p.fmode == 0) hipLaunchKernelGGL((wide_dalpha_kernel<0>), dim3(grid), dim3(256), 0, s, da);
-      else if (p.fmode == 1) hipLaunchKernelGGL((wide_dalpha_kernel<1>), dim3(grid), dim3(256), 0, s, da);
-      else hipLaunchKernelGGL((wide_dalpha_kernel<2>), dim3(grid), dim3(256), 0, s, da);
+      const unsigned dgrid = (unsigned)(BH * Kp * (2 * Kp + 1));  // 64 x 64 tiles
+      if (p.fmode == 0) hipLaunchKernelGGL((wide_dalpha_kernel<0>), dim3(dgrid), dim3(256), 0, s, da);
+      else if (p.fmode == 1) hipLaunchKernelGGL((wide_dalpha_kernel<1>), dim3(dgrid), dim3(256), 0, s, da);
+      else hipLaunchKernelGGL((wide_dalpha_kernel<2>), dim3(dgrid), dim3(256), 0, s, da);
       hipLaunchKernelGGL(wide_colsum_reduce, dim3(rgrid), dim3(256), 0, s, da, f.dalpha, 1.f);
     }
     timing_end(GRADLEV_K_WIDE_SCORE, s);
@@ -1152,7 +1179,7 @@ static hipError_t wide_bwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
   if (f.dW0) {
     WDw0Args wa{f.X, f.dY, f.dW0, p.B, p.H, p.T, p.d, p.m};
     timing_begin(GRADLEV_K_WIDE_OUT, s);
-    hipLaunchKernelGGL((wide_dw0_kernel<OP>), dim3((unsigned)(p.H * (p.m / 128) * (p.d / 128))), dim3(256), 0, s, wa);
+    hipLaunchKernelGGL((wide_dw0_kernel<OP>), dim3((unsigned)(p.H * (p.m / 128) * (p.d / 128))), dim3(512), 0, s, wa);
     timing_end(GRADLEV_K_WIDE_OUT, s);
   }
   return hipGetLastError();

@@ -1,0 +1,31 @@
+"""Wide backward with split score contractions: the gate gradients take dY G^T
+from the read's finish and X X^T from the split's partials, whichever other
+outputs are asked for.  Widths with one and with both contractions split."""
+
+import numpy as np
+import pytest
+
+from oracle import gradlev_oracle as orc
+from parity_util import check, log, to_host
+from test_gpu_wide import WIDE_BWD, dev_inputs, inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_2609_34174_amd as gl  # noqa: E402
+
+
+@pytest.mark.parametrize("dtype,d,m", [("bf16", 512, 1024), ("bf16", 256, 1024), ("f32", 1024, 256)])
+def test_wide_split_gate_gradients(dtype, d, m):
+    log(f"wide split dtype={dtype} d={d} m={m}")
+    inp = inputs(1, 1, 193, d, m, dtype, seed=6, alpha_kind="family", eta_kind="token", with_reset=True)
+    W0, X, G, dY, e, a, r = dev_inputs(inp, dtype)
+    full = {k: to_host(v) for k, v in gl.scan_bwd_gated(W0, X, G, dY, e, a, r, outputs=WIDE_BWD).items()}
+    ref = orc.scan_bwd(inp["W0"], inp["X"], inp["G"], inp["eta"], inp["dY"], alpha=inp["alpha"], reset=inp["reset"])
+    for k in WIDE_BWD:
+        check(k, full[k], ref[k], dtype)
+    for subset in (("deta",), ("dalpha",), ("deta", "dg"), ("gtilde", "deta"), ("dx", "dg", "dalpha")):
+        log(f"  subset {subset}")
+        part = gl.scan_bwd_gated(W0, X, G, dY, e, a, r, outputs=subset)
+        for k in subset:
+            np.testing.assert_array_equal(to_host(part[k]), full[k], err_msg=str(subset))
