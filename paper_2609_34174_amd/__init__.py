@@ -18,6 +18,7 @@ three the same); eta a float or an fp32 [B,H,T] tensor.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -179,22 +180,38 @@ def saved_bytes(shape: Shape):
 # torch marshalling
 # ---------------------------------------------------------------------------
 
-def _torch():
-    import torch
-    return torch
+_torch_mod = None
 
+
+def _torch():
+    global _torch_mod
+    if _torch_mod is None:
+        import torch
+        _torch_mod = torch
+    return _torch_mod
+
+
+# A call of the smallest layers is bound by the host (fp32, 256 tokens: forward
+# and backward 50 us of Python and launches), so what follows keeps to one test
+# per tensor, passes plain integers to ctypes and looks sizes up by shape.
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(device):
     torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None and device.index is not None:
+        return raw(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _check_dev(name, t, dtype=None, shape=None):
     torch = _torch()
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype)
+            and (shape is None or t.shape == shape)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -207,24 +224,45 @@ def _check_dev(name, t, dtype=None, shape=None):
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
+_shape_of = functools.lru_cache(maxsize=1024)(make_shape)
+
+
+class _Dims:
+    """A scan's sizes as Python integers, its C shape and that shape's key."""
+
+    __slots__ = ("B", "H", "T", "d_in", "d_out", "key", "c")
+
+
+def _sizes(query):
+    """`query` (of a Shape) by shape key: the planner's answers depend on nothing else."""
+    @functools.lru_cache(maxsize=1024)
+    def of(*key):
+        return query(_shape_of(*key))
+    return of
+
+
 def _scan_shape(W0, X, G, prefix, chunk, segment):
     torch = _torch()
     _check_dev("X", X)
     if X.dim() != 4:
         raise ValueError("X must be [B, H, T, d]")
     B, H, T, d = X.shape
-    if X.dtype == torch.bfloat16:
+    if X.dtype is torch.bfloat16:
         dt = BF16
-    elif X.dtype == torch.float32:
+    elif X.dtype is torch.float32:
         dt = F32
     else:
         raise TypeError("X must be float32 or bfloat16")
     _check_dev("G", G, X.dtype)
-    if G.dim() != 4 or tuple(G.shape[:3]) != (B, H, T):
+    if G.dim() != 4 or G.shape[:3] != (B, H, T):
         raise ValueError("G must be [B, H, T, m]")
     m = G.shape[3]
     _check_dev("W0", W0, torch.float32, (H, m, d))
-    return make_shape(B, H, T, d, m, dt, prefix, chunk, segment)
+    s = _Dims()
+    s.B, s.H, s.T, s.d_in, s.d_out = B, H, T, d, m
+    s.key = (B, H, T, d, m, dt, prefix, int(chunk), int(segment))
+    s.c = _shape_of(*s.key)
+    return s
 
 
 def _eta_args(eta, B, H, T, X):
@@ -237,28 +275,54 @@ def _eta_args(eta, B, H, T, X):
     return None, float(eta)
 
 
-def _workspace(shape, device, workspace):
-    torch = _torch()
-    need = workspace_bytes(shape)
+_scan_need = _sizes(workspace_bytes)
+_saved_need = _sizes(saved_bytes)
+
+
+def _workspace(need, device, workspace):
+    """The caller's workspace (checked) or a new one, and its size in bytes."""
     if need == 0:
         return None, 0
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
-    if workspace.numel() * workspace.element_size() < need:
+        return _torch().empty(need, dtype=_torch().uint8, device=device), need
+    have = workspace.numel() * workspace.element_size()
+    if have < need:
         raise ValueError(f"workspace too small: need {need} bytes")
-    return workspace, workspace.numel() * workspace.element_size()
+    return workspace, have
+
+
+def _out(out, shape, device):
+    """The caller's fp32 output (checked) or a new one."""
+    torch = _torch()
+    if out is None:
+        return torch.empty(shape, dtype=torch.float32, device=device)
+    _check_dev("out", out, torch.float32, shape)
+    return out
+
+
+def _grads(s, outputs, out, known, device):
+    """The dict of requested backward outputs, those not supplied allocated."""
+    torch = _torch()
+    x, g, t = (s.B, s.H, s.T, s.d_in), (s.B, s.H, s.T, s.d_out), (s.B, s.H, s.T)
+    sizes = {"gtilde": x, "dx": x, "dg": g, "deta": t, "dalpha": t, "dw0": (s.H, s.d_out, s.d_in)}
+    res = dict(out) if out else {}
+    for k in outputs:
+        if k not in known:
+            raise ValueError(f"unknown output {k!r}")
+        if k in res:
+            _check_dev(k, res[k], torch.float32, sizes[k])
+        else:
+            res[k] = torch.empty(sizes[k], dtype=torch.float32, device=device)
+    return res
 
 
 def scan_fwd(W0, X, G, eta=0.1, *, prefix="exclusive", chunk=0, segment=0, out=None, workspace=None):
     """Forward scan; returns Y [B,H,T,m] fp32 (see gradlev_scan_fwd)."""
-    torch = _torch()
     s = _scan_shape(W0, X, G, prefix, chunk, segment)
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
-    if out is None:
-        out = torch.empty(s.B, s.H, s.T, s.d_out, dtype=torch.float32, device=X.device)
-    _check_dev("out", out, torch.float32, (s.B, s.H, s.T, s.d_out))
-    ws, wsn = _workspace(s, X.device, workspace)
-    rc = lib().gradlev_scan_fwd(ctypes.byref(s), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(out),
+    out = _out(out, (s.B, s.H, s.T, s.d_out), X.device)
+    ws, wsn = _workspace(_scan_need(*s.key), X.device, workspace)
+    rc = lib().gradlev_scan_fwd(ctypes.byref(s.c), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(out),
                                 _ptr(ws), wsn, _stream(X.device))
     if rc != OK:
         raise GradLevError(rc, "gradlev_scan_fwd")
@@ -272,11 +336,9 @@ def scan_fwd_static(W0, X, G, eta=0.1, *, prefix="exclusive", chunk=0, segment=0
     torch = _torch()
     s = _scan_shape(W0, X, G, prefix, chunk, segment)
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
-    if out is None:
-        out = torch.empty(s.B, s.H, s.T, s.d_out, dtype=torch.float32, device=X.device)
-    _check_dev("out", out, torch.float32, (s.B, s.H, s.T, s.d_out))
+    out = _out(out, (s.B, s.H, s.T, s.d_out), X.device)
     with torch.cuda.device(X.device):
-        rc = lib().gradlev_scan_fwd_static(ctypes.byref(s), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(out),
+        rc = lib().gradlev_scan_fwd_static(ctypes.byref(s.c), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(out),
                                            _stream(X.device))
     if rc != OK:
         raise GradLevError(rc, "gradlev_scan_fwd_static")
@@ -293,21 +355,12 @@ def scan_bwd(W0, X, G, dY, eta=0.1, *, prefix="exclusive", chunk=0, segment=0,
     outputs: any of "gtilde" [B,H,T,d], "dx" [B,H,T,d], "dg" [B,H,T,m],
     "deta" [B,H,T], "dw0" [H,m,d] (all fp32).  ``out`` may pre-supply tensors.
     """
-    torch = _torch()
     s = _scan_shape(W0, X, G, prefix, chunk, segment)
     _check_dev("dY", dY, X.dtype, (s.B, s.H, s.T, s.d_out))
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
-    shapes = {"gtilde": (s.B, s.H, s.T, s.d_in), "dx": (s.B, s.H, s.T, s.d_in),
-              "dg": (s.B, s.H, s.T, s.d_out), "deta": (s.B, s.H, s.T), "dw0": (s.H, s.d_out, s.d_in)}
-    res = dict(out or {})
-    for k in outputs:
-        if k not in shapes:
-            raise ValueError(f"unknown output {k!r}")
-        if k not in res:
-            res[k] = torch.empty(shapes[k], dtype=torch.float32, device=X.device)
-        _check_dev(k, res[k], torch.float32, shapes[k])
-    ws, wsn = _workspace(s, X.device, workspace)
-    rc = lib().gradlev_scan_bwd(ctypes.byref(s), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(dY),
+    res = _grads(s, outputs, out, BWD_OUTPUTS, X.device)
+    ws, wsn = _workspace(_scan_need(*s.key), X.device, workspace)
+    rc = lib().gradlev_scan_bwd(ctypes.byref(s.c), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(dY),
                                 _ptr(res.get("gtilde")), _ptr(res.get("dx")), _ptr(res.get("dg")),
                                 _ptr(res.get("deta")), _ptr(res.get("dw0")), _ptr(ws), wsn,
                                 _stream(X.device))
@@ -317,7 +370,6 @@ def scan_bwd(W0, X, G, dY, eta=0.1, *, prefix="exclusive", chunk=0, segment=0,
 
 
 def _bytes_of(name, t, need):
-    torch = _torch()
     if t is None:
         return None, 0
     _check_dev(name, t)
@@ -336,17 +388,15 @@ def scan_fwd_save(W0, X, G, eta=0.1, *, prefix="exclusive", chunk=0, segment=0, 
     torch = _torch()
     s = _scan_shape(W0, X, G, prefix, chunk, segment)
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
-    sv_need, ws_need = saved_bytes(s)
-    if out is None:
-        out = torch.empty(s.B, s.H, s.T, s.d_out, dtype=torch.float32, device=X.device)
-    _check_dev("out", out, torch.float32, (s.B, s.H, s.T, s.d_out))
+    sv_need, ws_need = _saved_need(*s.key)
+    out = _out(out, (s.B, s.H, s.T, s.d_out), X.device)
     if saved is None:
         saved = torch.empty(sv_need // 4, dtype=torch.float32, device=X.device)
     saved, svn = _bytes_of("saved", saved, sv_need)
     if workspace is None and ws_need:
         workspace = torch.empty(ws_need, dtype=torch.uint8, device=X.device)
     ws, wsn = _bytes_of("workspace", workspace, ws_need)
-    rc = lib().gradlev_scan_fwd_save(ctypes.byref(s), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(out),
+    rc = lib().gradlev_scan_fwd_save(ctypes.byref(s.c), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(out),
                                      _ptr(saved), svn, _ptr(ws), wsn, _stream(X.device))
     if rc != OK:
         raise GradLevError(rc, "gradlev_scan_fwd_save")
@@ -361,21 +411,13 @@ def scan_bwd_saved(W0, X, G, dY, saved, eta=0.1, *, prefix="exclusive", chunk=0,
     s = _scan_shape(W0, X, G, prefix, chunk, segment)
     _check_dev("dY", dY, X.dtype, (s.B, s.H, s.T, s.d_out))
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
-    sv_need, ws_need = saved_bytes(s)
-    shapes = {"gtilde": (s.B, s.H, s.T, s.d_in), "dx": (s.B, s.H, s.T, s.d_in),
-              "dg": (s.B, s.H, s.T, s.d_out), "deta": (s.B, s.H, s.T), "dw0": (s.H, s.d_out, s.d_in)}
-    res = dict(out or {})
-    for k in outputs:
-        if k not in shapes:
-            raise ValueError(f"unknown output {k!r}")
-        if k not in res:
-            res[k] = torch.empty(shapes[k], dtype=torch.float32, device=X.device)
-        _check_dev(k, res[k], torch.float32, shapes[k])
+    sv_need, ws_need = _saved_need(*s.key)
+    res = _grads(s, outputs, out, BWD_OUTPUTS, X.device)
     saved, svn = _bytes_of("saved", saved, sv_need)
     if workspace is None and ws_need:
         workspace = torch.empty(ws_need, dtype=torch.uint8, device=X.device)
     ws, wsn = _bytes_of("workspace", workspace, ws_need)
-    rc = lib().gradlev_scan_bwd_saved(ctypes.byref(s), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(dY),
+    rc = lib().gradlev_scan_bwd_saved(ctypes.byref(s.c), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(dY),
                                       _ptr(saved), svn, _ptr(res.get("gtilde")), _ptr(res.get("dx")),
                                       _ptr(res.get("dg")), _ptr(res.get("deta")), _ptr(res.get("dw0")),
                                       _ptr(ws), wsn, _stream(X.device))
@@ -392,6 +434,9 @@ def reset_saved_bytes(shape: Shape):
     if rc != OK:
         raise GradLevError(rc, "gradlev_scan_reset_saved_bytes")
     return int(sv.value), int(ws.value)
+
+
+_reset_need = _sizes(reset_saved_bytes)
 
 
 def _reset_arg(reset, B, T, X):
@@ -411,17 +456,15 @@ def scan_fwd_reset_save(W0, X, G, eta=0.1, reset=None, *, segment=0, out=None, s
     s = _scan_shape(W0, X, G, "exclusive", 0, segment)
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
     r = _reset_arg(reset, s.B, s.T, X)
-    sv_need, ws_need = reset_saved_bytes(s)
-    if out is None:
-        out = torch.empty(s.B, s.H, s.T, s.d_out, dtype=torch.float32, device=X.device)
-    _check_dev("out", out, torch.float32, (s.B, s.H, s.T, s.d_out))
+    sv_need, ws_need = _reset_need(*s.key)
+    out = _out(out, (s.B, s.H, s.T, s.d_out), X.device)
     if saved is None:
         saved = torch.empty(sv_need // 4, dtype=torch.float32, device=X.device)
     saved, svn = _bytes_of("saved", saved, sv_need)
     if workspace is None and ws_need:
         workspace = torch.empty(ws_need, dtype=torch.uint8, device=X.device)
     ws, wsn = _bytes_of("workspace", workspace, ws_need)
-    rc = lib().gradlev_scan_fwd_reset_save(ctypes.byref(s), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(r),
+    rc = lib().gradlev_scan_fwd_reset_save(ctypes.byref(s.c), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(r),
                                            _ptr(out), _ptr(saved), svn, _ptr(ws), wsn, _stream(X.device))
     if rc != OK:
         raise GradLevError(rc, "gradlev_scan_fwd_reset_save")
@@ -437,21 +480,13 @@ def scan_bwd_reset_saved(W0, X, G, dY, saved, eta=0.1, reset=None, *, segment=0,
     _check_dev("dY", dY, X.dtype, (s.B, s.H, s.T, s.d_out))
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
     r = _reset_arg(reset, s.B, s.T, X)
-    sv_need, ws_need = reset_saved_bytes(s)
+    sv_need, ws_need = _reset_need(*s.key)
     saved, svn = _bytes_of("saved", saved, sv_need)
-    shapes = {"gtilde": (s.B, s.H, s.T, s.d_in), "dx": (s.B, s.H, s.T, s.d_in),
-              "dg": (s.B, s.H, s.T, s.d_out), "deta": (s.B, s.H, s.T), "dw0": (s.H, s.d_out, s.d_in)}
-    res = dict(out or {})
-    for k in outputs:
-        if k not in shapes:
-            raise ValueError(f"unknown output {k!r}")
-        if k not in res:
-            res[k] = torch.empty(shapes[k], dtype=torch.float32, device=X.device)
-        _check_dev(k, res[k], torch.float32, shapes[k])
+    res = _grads(s, outputs, out, BWD_OUTPUTS, X.device)
     if workspace is None and ws_need:
         workspace = torch.empty(ws_need, dtype=torch.uint8, device=X.device)
     ws, wsn = _bytes_of("workspace", workspace, ws_need)
-    rc = lib().gradlev_scan_bwd_reset_saved(ctypes.byref(s), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(dY),
+    rc = lib().gradlev_scan_bwd_reset_saved(ctypes.byref(s.c), _ptr(W0), _ptr(X), _ptr(G), _ptr(e), es, _ptr(dY),
                                             _ptr(r), _ptr(saved), svn, _ptr(res.get("gtilde")), _ptr(res.get("dx")),
                                             _ptr(res.get("dg")), _ptr(res.get("deta")), _ptr(res.get("dw0")),
                                             _ptr(ws), wsn, _stream(X.device))
@@ -473,9 +508,7 @@ def decode_step(W, x, g, eta=0.1, *, out=None):
         e, es = eta, 0.0
     else:
         e, es = None, float(eta)
-    if out is None:
-        out = torch.empty(S, H, m, dtype=torch.float32, device=W.device)
-    _check_dev("out", out, torch.float32, (S, H, m))
+    out = _out(out, (S, H, m), W.device)
     rc = lib().gradlev_decode_step(S, H, d, m, _ptr(W), _ptr(x), _ptr(g), _ptr(e), es, _ptr(out),
                                    _stream(W.device))
     if rc != OK:
@@ -511,30 +544,18 @@ def _gates(alpha, reset, B, H, T, X, name="alpha", alpha_shape=None):
     return g
 
 
-def _gated_ws(shape, device, workspace):
-    torch = _torch()
-    need = gated_workspace_bytes(shape)
-    if need == 0:
-        return None, 0
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
-    if workspace.numel() * workspace.element_size() < need:
-        raise ValueError(f"workspace too small: need {need} bytes")
-    return workspace, workspace.numel() * workspace.element_size()
+_gated_need = _sizes(gated_workspace_bytes)
 
 
 def scan_fwd_gated(W0, X, G, eta=0.1, alpha=1.0, reset=None, *, chunk=0, segment=0, out=None,
                    workspace=None):
     """Gated forward scan (retention alpha: float or fp32 [B,H,T]; reset: uint8 [B,T] or None)."""
-    torch = _torch()
     s = _scan_shape(W0, X, G, "exclusive", chunk, segment)
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
     gt = _gates(alpha, reset, s.B, s.H, s.T, X)
-    if out is None:
-        out = torch.empty(s.B, s.H, s.T, s.d_out, dtype=torch.float32, device=X.device)
-    _check_dev("out", out, torch.float32, (s.B, s.H, s.T, s.d_out))
-    ws, wsn = _gated_ws(s, X.device, workspace)
-    rc = lib().gradlev_scan_fwd_gated(ctypes.byref(s), ctypes.byref(gt), _ptr(W0), _ptr(X), _ptr(G), _ptr(e),
+    out = _out(out, (s.B, s.H, s.T, s.d_out), X.device)
+    ws, wsn = _workspace(_gated_need(*s.key), X.device, workspace)
+    rc = lib().gradlev_scan_fwd_gated(ctypes.byref(s.c), ctypes.byref(gt), _ptr(W0), _ptr(X), _ptr(G), _ptr(e),
                                       es, _ptr(out), _ptr(ws), wsn, _stream(X.device))
     if rc != OK:
         raise GradLevError(rc, "gradlev_scan_fwd_gated")
@@ -547,23 +568,13 @@ GATED_OUTPUTS = ("gtilde", "dx", "dg", "deta", "dalpha", "dw0")
 def scan_bwd_gated(W0, X, G, dY, eta=0.1, alpha=1.0, reset=None, *, chunk=0, segment=0,
                    outputs=GATED_OUTPUTS, out=None, workspace=None):
     """Backward of the gated forward scan; dict with the requested outputs (``dalpha`` [B,H,T] too)."""
-    torch = _torch()
     s = _scan_shape(W0, X, G, "exclusive", chunk, segment)
     _check_dev("dY", dY, X.dtype, (s.B, s.H, s.T, s.d_out))
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
     gt = _gates(alpha, reset, s.B, s.H, s.T, X)
-    shapes = {"gtilde": (s.B, s.H, s.T, s.d_in), "dx": (s.B, s.H, s.T, s.d_in),
-              "dg": (s.B, s.H, s.T, s.d_out), "deta": (s.B, s.H, s.T), "dalpha": (s.B, s.H, s.T),
-              "dw0": (s.H, s.d_out, s.d_in)}
-    res = dict(out or {})
-    for k in outputs:
-        if k not in shapes:
-            raise ValueError(f"unknown output {k!r}")
-        if k not in res:
-            res[k] = torch.empty(shapes[k], dtype=torch.float32, device=X.device)
-        _check_dev(k, res[k], torch.float32, shapes[k])
-    ws, wsn = _gated_ws(s, X.device, workspace)
-    rc = lib().gradlev_scan_bwd_gated(ctypes.byref(s), ctypes.byref(gt), _ptr(W0), _ptr(X), _ptr(G), _ptr(e),
+    res = _grads(s, outputs, out, GATED_OUTPUTS, X.device)
+    ws, wsn = _workspace(_gated_need(*s.key), X.device, workspace)
+    rc = lib().gradlev_scan_bwd_gated(ctypes.byref(s.c), ctypes.byref(gt), _ptr(W0), _ptr(X), _ptr(G), _ptr(e),
                                       es, _ptr(dY), _ptr(res.get("gtilde")), _ptr(res.get("dx")),
                                       _ptr(res.get("dg")), _ptr(res.get("deta")), _ptr(res.get("dalpha")),
                                       _ptr(res.get("dw0")), _ptr(ws), wsn, _stream(X.device))
@@ -581,6 +592,9 @@ def gated_saved_bytes(shape: Shape):
     return int(sv.value), int(ws.value)
 
 
+_gated_saved_need = _sizes(gated_saved_bytes)
+
+
 def scan_fwd_gated_save(W0, X, G, eta=0.1, alpha=1.0, reset=None, *, chunk=0, segment=0, out=None, saved=None,
                         workspace=None):
     """Gated forward that also keeps the backward's chunk-start states.
@@ -590,17 +604,15 @@ def scan_fwd_gated_save(W0, X, G, eta=0.1, alpha=1.0, reset=None, *, chunk=0, se
     s = _scan_shape(W0, X, G, "exclusive", chunk, segment)
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
     gt = _gates(alpha, reset, s.B, s.H, s.T, X)
-    sv_need, ws_need = gated_saved_bytes(s)
-    if out is None:
-        out = torch.empty(s.B, s.H, s.T, s.d_out, dtype=torch.float32, device=X.device)
-    _check_dev("out", out, torch.float32, (s.B, s.H, s.T, s.d_out))
+    sv_need, ws_need = _gated_saved_need(*s.key)
+    out = _out(out, (s.B, s.H, s.T, s.d_out), X.device)
     if saved is None:
         saved = torch.empty(sv_need // 4, dtype=torch.float32, device=X.device)
     saved, svn = _bytes_of("saved", saved, sv_need)
     if workspace is None and ws_need:
         workspace = torch.empty(ws_need, dtype=torch.uint8, device=X.device)
     ws, wsn = _bytes_of("workspace", workspace, ws_need)
-    rc = lib().gradlev_scan_fwd_gated_save(ctypes.byref(s), ctypes.byref(gt), _ptr(W0), _ptr(X), _ptr(G), _ptr(e),
+    rc = lib().gradlev_scan_fwd_gated_save(ctypes.byref(s.c), ctypes.byref(gt), _ptr(W0), _ptr(X), _ptr(G), _ptr(e),
                                            es, _ptr(out), _ptr(saved), svn, _ptr(ws), wsn, _stream(X.device))
     if rc != OK:
         raise GradLevError(rc, "gradlev_scan_fwd_gated_save")
@@ -615,22 +627,13 @@ def scan_bwd_gated_saved(W0, X, G, dY, saved, eta=0.1, alpha=1.0, reset=None, *,
     _check_dev("dY", dY, X.dtype, (s.B, s.H, s.T, s.d_out))
     e, es = _eta_args(eta, s.B, s.H, s.T, X)
     gt = _gates(alpha, reset, s.B, s.H, s.T, X)
-    sv_need, ws_need = gated_saved_bytes(s)
-    shapes = {"gtilde": (s.B, s.H, s.T, s.d_in), "dx": (s.B, s.H, s.T, s.d_in),
-              "dg": (s.B, s.H, s.T, s.d_out), "deta": (s.B, s.H, s.T), "dalpha": (s.B, s.H, s.T),
-              "dw0": (s.H, s.d_out, s.d_in)}
-    res = dict(out or {})
-    for k in outputs:
-        if k not in shapes:
-            raise ValueError(f"unknown output {k!r}")
-        if k not in res:
-            res[k] = torch.empty(shapes[k], dtype=torch.float32, device=X.device)
-        _check_dev(k, res[k], torch.float32, shapes[k])
+    sv_need, ws_need = _gated_saved_need(*s.key)
+    res = _grads(s, outputs, out, GATED_OUTPUTS, X.device)
     saved, svn = _bytes_of("saved", saved, sv_need)
     if workspace is None and ws_need:
         workspace = torch.empty(ws_need, dtype=torch.uint8, device=X.device)
     ws, wsn = _bytes_of("workspace", workspace, ws_need)
-    rc = lib().gradlev_scan_bwd_gated_saved(ctypes.byref(s), ctypes.byref(gt), _ptr(W0), _ptr(X), _ptr(G),
+    rc = lib().gradlev_scan_bwd_gated_saved(ctypes.byref(s.c), ctypes.byref(gt), _ptr(W0), _ptr(X), _ptr(G),
                                             _ptr(e), es, _ptr(dY), _ptr(saved), svn, _ptr(res.get("gtilde")),
                                             _ptr(res.get("dx")), _ptr(res.get("dg")), _ptr(res.get("deta")),
                                             _ptr(res.get("dalpha")), _ptr(res.get("dw0")), _ptr(ws), wsn,
@@ -662,9 +665,7 @@ def decode_step_gated(W, W0, x, g, eta=0.1, alpha=1.0, reset=None, *, out=None):
         a, as_ = None, float(alpha)
     if reset is not None:
         _check_dev("reset", reset, torch.uint8, (S,))
-    if out is None:
-        out = torch.empty(S, H, m, dtype=torch.float32, device=W.device)
-    _check_dev("out", out, torch.float32, (S, H, m))
+    out = _out(out, (S, H, m), W.device)
     rc = lib().gradlev_decode_step_gated(S, H, d, m, _ptr(W), _ptr(W0), _ptr(x), _ptr(g), _ptr(e), es,
                                          _ptr(a), as_, _ptr(reset), _ptr(out), _stream(W.device))
     if rc != OK:
@@ -697,18 +698,18 @@ def _mlp_shape(W10, W20, X, Gz, Gy, act, segment):
     return MlpShape(B, H, T, d, hid, o, int(segment), BF16 if X.dtype == torch.bfloat16 else F32, ACT[act])
 
 
-def _mlp_ws(s, device, workspace):
-    torch = _torch()
+@functools.lru_cache(maxsize=1024)
+def _mlp_need(*key):
     n = ctypes.c_size_t(0)
-    rc = lib().gradlev_mlp_workspace_bytes(ctypes.byref(s), ctypes.byref(n))
+    rc = lib().gradlev_mlp_workspace_bytes(ctypes.byref(MlpShape(*key)), ctypes.byref(n))
     if rc != OK:
         raise GradLevError(rc, "gradlev_mlp_workspace_bytes")
-    need = max(int(n.value), 256)
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
-    if workspace.numel() * workspace.element_size() < need:
-        raise ValueError(f"workspace too small: need {need} bytes")
-    return workspace, workspace.numel() * workspace.element_size()
+    return max(int(n.value), 256)
+
+
+def _mlp_ws(s, device, workspace):
+    need = _mlp_need(s.B, s.H, s.T, s.d_in, s.hidden, s.d_out, s.segment, s.in_dtype, s.act)
+    return _workspace(need, device, workspace)
 
 
 def mlp_fwd(W10, W20, X, Gz, Gy, mu=0.9, alpha=1.0, reset=None, *, act="tanh", segment=0, workspace=None):
