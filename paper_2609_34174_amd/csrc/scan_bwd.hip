@@ -176,49 +176,32 @@ bwd_main_kernel(const BArgs a) {
   // and Rj[ib] holds R[i][j = 16w + c], at the segment's end: W_0 - sum_{j<=seg} A_j
   // (subtracted in segment order) and R = sum_{j>seg} B_j (added from the last segment down).
   f32x4 Wj[NWB][IB], Rj[IB];
-  constexpr int PU = IB <= 4 ? 4 : 1;  // aggregates summed per batch of loads (register budget)
+  constexpr int PU = NWB * IB <= 4 ? 4 : 2;  // aggregates summed per batch of loads (register budget)
   if (w < JB) {
     // The segment's end state: saved by the forward, or W_0 minus the
     // aggregated writes up to and including this segment.
     const float* w0 = a.wend ? a.wend + (bh * a.nseg + seg) * M * D : a.W0 + (bh % a.H) * M * D;
+    f32x4 ws[NWB * IB];
 #pragma unroll
-    for (int e = 0; e < NWB; ++e) {
+    for (int e = 0; e < NWB; ++e)
 #pragma unroll
       for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Wj[e][ib][r] = w0[(int64_t)(16 * ib + 4 * q + r) * D + 16 * blk(e) + c];
-      const int64_t o = bh * a.nseg * M * D + (int64_t)(16 * blk(e) + c) * M + 4 * q;
-      for (int64_t j0 = 0; !a.wend && j0 <= seg; j0 += PU) {
-        f32x4 v[PU][IB];
+        for (int r = 0; r < 4; ++r) ws[e * IB + ib][r] = w0[(int64_t)(16 * ib + 4 * q + r) * D + 16 * blk(e) + c];
+    const int64_t o = bh * a.nseg * M * D + 4 * q;
+    const float* A = a.aggA + o + (int64_t)(16 * blk(0) + c) * M;  // column block e lies 16 M floats after e - 1
+    sum_segments<PU, true>(ws, a.wend ? 0 : (int)seg + 1, [&](int k) { return A + (int64_t)k * M * D; },
+                           [](int i) { return i / IB * 16 * M + i % IB * 16; });
 #pragma unroll
-        for (int u = 0; u < PU; ++u)
+    for (int e = 0; e < NWB; ++e)
 #pragma unroll
-          for (int ib = 0; ib < IB; ++ib)
-            v[u][ib] = j0 + u <= seg ? *reinterpret_cast<const f32x4*>(a.aggA + o + (j0 + u) * M * D + 16 * ib) : zero4();
-#pragma unroll
-        for (int u = 0; u < PU; ++u)
-#pragma unroll
-          for (int ib = 0; ib < IB; ++ib)
-            if (j0 + u <= seg) Wj[e][ib] -= v[u][ib];
-      }
-    }
-    const int64_t o = bh * a.nseg * M * D + (int64_t)(16 * w + c) * M + 4 * q;
+      for (int ib = 0; ib < IB; ++ib) Wj[e][ib] = ws[e * IB + ib];
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib) Rj[ib] = zero4();
     if (FULL && a.aggB && !no_sfx) {
-      for (int64_t j0 = j_last; j0 > seg; j0 -= PU) {
-        f32x4 v[PU][IB];
-#pragma unroll
-        for (int u = 0; u < PU; ++u)
-#pragma unroll
-          for (int ib = 0; ib < IB; ++ib)
-            v[u][ib] = j0 - u > seg ? *reinterpret_cast<const f32x4*>(a.aggB + o + (j0 - u) * M * D + 16 * ib) : zero4();
-#pragma unroll
-        for (int u = 0; u < PU; ++u)
-#pragma unroll
-          for (int ib = 0; ib < IB; ++ib)
-            if (j0 - u > seg) Rj[ib] += v[u][ib];
-      }
+      const float* Bk = a.aggB + o + (int64_t)(16 * w + c) * M;
+      sum_segments<IB <= 4 ? 4 : 2, false>(Rj, (int)(j_last - seg), [&](int k) { return Bk + (j_last - k) * M * D; },
+                                           [](int ib) { return 16 * ib; });
     }
   }
   for (int i = tid; i < C * C; i += NT) Es[i] = (E)0.f;
@@ -777,41 +760,19 @@ bwd_split_kernel(const BArgs a) {
   f32x4 St[IB];
   constexpr int PU = IB <= 4 ? 4 : 1;  // aggregates summed per batch of loads (register budget)
   const int64_t ao = bh * a.nseg * M * D + (int64_t)(16 * wb + c) * M + 4 * q;
+  auto at = [](int ib) { return 16 * ib; };
   if (gw) {
     const float* w0 = a.wend ? a.wend + (bh * a.nseg + seg) * M * D : a.W0 + (bh % a.H) * M * D;
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
       for (int r = 0; r < 4; ++r) St[ib][r] = w0[(int64_t)(16 * ib + 4 * q + r) * D + 16 * wb + c];
-    for (int64_t j0 = 0; !a.wend && j0 <= seg; j0 += PU) {
-      f32x4 v[PU][IB];
-#pragma unroll
-      for (int u = 0; u < PU; ++u)
-#pragma unroll
-        for (int ib = 0; ib < IB; ++ib)
-          v[u][ib] = j0 + u <= seg ? *reinterpret_cast<const f32x4*>(a.aggA + ao + (j0 + u) * M * D + 16 * ib) : zero4();
-#pragma unroll
-      for (int u = 0; u < PU; ++u)
-#pragma unroll
-        for (int ib = 0; ib < IB; ++ib)
-          if (j0 + u <= seg) St[ib] -= v[u][ib];
-    }
+    sum_segments<PU, true>(St, a.wend ? 0 : (int)seg + 1, [&](int k) { return a.aggA + ao + (int64_t)k * M * D; }, at);
   } else {
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib) St[ib] = zero4();
-    for (int64_t j0 = a.nseg - 1; a.aggB && j0 > seg; j0 -= PU) {
-      f32x4 v[PU][IB];
-#pragma unroll
-      for (int u = 0; u < PU; ++u)
-#pragma unroll
-        for (int ib = 0; ib < IB; ++ib)
-          v[u][ib] = j0 - u > seg ? *reinterpret_cast<const f32x4*>(a.aggB + ao + (j0 - u) * M * D + 16 * ib) : zero4();
-#pragma unroll
-      for (int u = 0; u < PU; ++u)
-#pragma unroll
-        for (int ib = 0; ib < IB; ++ib)
-          if (j0 - u > seg) St[ib] += v[u][ib];
-    }
+    if (a.aggB)
+      sum_segments<PU, false>(St, (int)(a.nseg - 1 - seg), [&](int k) { return a.aggB + ao + (a.nseg - 1 - k) * M * D; }, at);
   }
   for (int i = tid; i < C * C; i += NT) Es[i] = (E)0.f;
   if constexpr (SSH) {
@@ -1265,7 +1226,9 @@ static hipError_t bwd_dispatch2(const ScanProblem& p, const BwdPtrs& f, hipStrea
   b.deta = f.deta;
   b.aggA = f.aggA;
   b.aggB = need_sfx ? f.aggB : nullptr;
-  b.rfin = f.dW0 ? f.rfin : nullptr;
+  // One batch row: its sums are dW0 itself, and the reduction is not launched.
+  const bool sum_b = f.dW0 && p.B > 1;
+  b.rfin = sum_b ? f.rfin : f.dW0;
   b.wend = f.wend;
   timing_begin(GRADLEV_K_BWD_MAIN, s);
   if (read_only) {
@@ -1290,7 +1253,7 @@ static hipError_t bwd_dispatch2(const ScanProblem& p, const BwdPtrs& f, hipStrea
     }
   }
   timing_end(GRADLEV_K_BWD_MAIN, s);
-  if (f.dW0) {
+  if (sum_b) {
     const int64_t md4 = (int64_t)D * M / 4, n = p.H * md4;
     timing_begin(GRADLEV_K_BWD_DW0, s);
     hipLaunchKernelGGL(reduce_dw0_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, f.rfin, f.dW0, p.B, p.H, md4);

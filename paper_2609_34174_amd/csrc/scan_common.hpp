@@ -308,6 +308,32 @@ __device__ __forceinline__ int64_t first_reset_in(rsrc_t row, int64_t lo, int64_
   return -1;
 }
 
+// s[i] += (SUB: -=) the aggregates of n segments, the k-th at p(k) + at(i)
+// floats: PU segments' loads are in flight together and added in order.  Past
+// the last one a batch reads it again and adds nothing, so that the loads need
+// no branch.
+template <int PU, bool SUB, int N, class P, class AT>
+__device__ __forceinline__ void sum_segments(f32x4 (&s)[N], int n, P p, AT at) {
+  for (int k = 0; k < n; k += PU) {
+    f32x4 v[PU][N];
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+      const float* b = p(k + u < n ? k + u : n - 1);
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[u][i] = *reinterpret_cast<const f32x4*>(b + at(i));
+    }
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+      if (k + u >= n) break;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        if constexpr (SUB) s[i] -= v[u][i];
+        else s[i] += v[u][i];
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Segment aggregates: A_k = sum_{t in seg k} eta_t g_t x_t^T (fp32) and, for
 // the backward (mode kAggBwdAB), B_k = sum_{t in seg k} dY_t x_t^T for k >= 1.

@@ -123,19 +123,8 @@ fwd_main_kernel(const KArgs a) {
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb) W0r[jb] = Ws[jb];
     const float* ag = a.aggA + bh * a.nseg * M * D + o;
-    for (int64_t j0 = j_first; !from_w0 && j0 < seg; j0 += 4) {
-      f32x4 v[4][JB];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb)
-          v[u][jb] = j0 + u < seg ? *reinterpret_cast<const f32x4*>(ag + (j0 + u) * M * D + 16 * jb) : zero4();
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb)
-          if (j0 + u < seg) Ws[jb] -= v[u][jb];
-    }
+    sum_segments<4, true>(Ws, from_w0 ? 0 : (int)(seg - j_first), [&](int k) { return ag + (j_first + k) * M * D; },
+                          [](int jb) { return 16 * jb; });
   }
   if constexpr (!RS)
     for (int i = tid; i < C * C; i += NT) Pl[i] = (E)0.f;
