@@ -1085,15 +1085,15 @@ reduce_dw0_segs_kernel(const float* aggF, float* dW0, int64_t B, int64_t H, int6
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-// Tile length of the backward (the same for both eta forms): 64 for the
+// Tile length of the backward (the same for both eta forms): 64 for the bf16
 // 64 x 64 map; 32 for maps with a 128-wide side, whose per-wave state and
 // accumulators do not fit the register budget at 64 (measured: the 128 x 128
-// bf16 backward runs 1.85x faster at 32).  launch_scan_bwd dispatches on
-// exactly this value.
+// bf16 backward runs 1.85x faster at 32).  fp32 64 x 64 takes 32 too unless 64
+// is asked for (as the reset pair does): its matrix steps cost eight times
+// bf16's, so the smaller in-chunk triangle pays (8 sequences, whole backward:
+// T = 256 27 -> 18 us, T = 4096 89 -> 78 us; 64 sequences of 1024 90 -> 80 us).
 int bwd_chunk_for(int bf16, int d, int m, int requested) {
-  (void)bf16;
-  (void)requested;
-  return (d == 64 && m == 64) ? 64 : 32;
+  return (d == 64 && m == 64 && (bf16 || requested == 64)) ? 64 : 32;
 }
 static_assert(lds_bytes_bwd(1, 64, 64, 64, 1) <= 160 * 1024, "bf16 backward tile does not fit LDS");
 static_assert(lds_bytes_bwd(1, 128, 128, 32, 1) <= 160 * 1024, "bf16 backward tile does not fit LDS");
@@ -1106,7 +1106,7 @@ SegCost bwd_seg_cost(int bf16, int d, int m) {
   static const SegCost bf[3] = {{5.2f, 4.8f, 0.36f, 7.6f, 0.81f, 4.9f, 2, 1.49f},
                                 {2.f, 1.6f, 0.74f, 10.2f, 0.83f, 8.6f, 1, 0.f},
                                 {6.4f, 5.4f, 0.7f, 8.2f, 1.94f, 10.3f, 1, 0.f}};
-  static const SegCost f32[3] = {{2.4f, 1.7f, 1.2f, 9.4f, 0.69f, 15.8f, 1, 0.f},
+  static const SegCost f32[3] = {{2.4f, 1.7f, 1.2f, 8.f, 0.6f, 13.5f, 2, 1.85f},
                                  {2.f, 2.f, 2.5f, 10.f, 0.9f, 24.f, 1, 0.f},
                                  {4.f, 4.f, 3.f, 9.f, 1.9f, 42.f, 1, 0.f}};
   return bf16 ? bf[wide] : f32[wide];
@@ -1278,7 +1278,7 @@ static hipError_t bwd_by_dims(const ScanProblem& p, const BwdPtrs& f, hipStream_
 }
 
 hipError_t launch_scan_bwd(const ScanProblem& p, const BwdPtrs& f, hipStream_t s) {
-  if (p.chunk != bwd_chunk_for(p.bf16, p.d, p.m, 0)) return hipErrorInvalidValue;
+  if (p.chunk != bwd_chunk_for(p.bf16, p.d, p.m, p.chunk)) return hipErrorInvalidValue;
   if (p.chunk == 64) return p.bf16 ? bwd_dispatch<OpBF16, 64, 64, 64>(p, f, s) : bwd_dispatch<OpF32, 64, 64, 64>(p, f, s);
   return p.bf16 ? bwd_by_dims<OpBF16, 32>(p, f, s) : bwd_by_dims<OpF32, 32>(p, f, s);
 }
