@@ -266,6 +266,12 @@ __device__ __forceinline__ float sum_q(float v) {
 // ---------------------------------------------------------------------------
 enum GAggMode { kGAggFwd = 0, kGAggBwd = 1, kGAggBwdSaved = 2 };
 
+// The gates of a chunk are at most 64 tokens, so every wave loads them, one
+// token per lane, and forms their products by itself: the row scales of its
+// share of the staged tiles go through a table of the wave's own (LDS is in
+// order within a wave), and no wave waits for another's scan.  With two
+// buffers (bf16) a chunk has one barrier; a scan by one wave, published to
+// the others, took four more.
 template <class OP, int D, int M, int C, int MODE>
 __global__ void __launch_bounds__(cmax(D, M) / 16 * 64)
 agg_gated_kernel(const GArgs a, int64_t nagg) {
@@ -276,14 +282,16 @@ agg_gated_kernel(const GArgs a, int64_t nagg) {
   constexpr int NW = cmax(D, M) / 16, NT = NW * 64;
   constexpr int JB = D / 16, IB = M / 16;
   constexpr bool SPL = OP::kSplit == 2;
-  __shared__ E Xs[C * D];
-  __shared__ E Vh[WA ? C * M : 1];
-  __shared__ E Vl[WA && SPL ? C * M : 1];
-  __shared__ E Ds[BWD ? C * M : 1];
-  __shared__ E Bh[BWD ? C * M : 1];
-  __shared__ E Bl[BWD && SPL ? C * M : 1];
-  __shared__ __attribute__((aligned(16))) float al[C], et[C], pre[C], suf[C], pin[C], sinv[C], vw[C], pw[C];
-  __shared__ float mid[16], tot;
+  constexpr int TILES = C * D + (WA ? (SPL ? 2 : 1) * C * M : 0) + (BWD ? (SPL ? 3 : 2) * C * M : 0);
+  constexpr bool DB = SPL && 2 * TILES * (int)sizeof(E) <= 100 * 1024;
+  constexpr int NB = DB ? 2 : 1;
+  __shared__ E Xs_[NB][C * D];
+  __shared__ E Vh_[NB][WA ? C * M : 1];
+  __shared__ E Vl_[NB][WA && SPL ? C * M : 1];
+  __shared__ E Ds_[NB][BWD ? C * M : 1];
+  __shared__ E Bh_[NB][BWD ? C * M : 1];
+  __shared__ E Bl_[NB][BWD && SPL ? C * M : 1];
+  __shared__ float vw[NW][WA ? C : 1], pw[NW][BWD ? C : 1];  // row scales of V and B, per wave
 
   int64_t bh, seg;
   if (!map_block(a.BH, a.nseg, bh, seg) || seg >= nagg) return;
@@ -312,7 +320,7 @@ agg_gated_kernel(const GArgs a, int64_t nagg) {
   GateReg ar[2];
   auto fetch = [&](int k, int64_t t0) {
     const bool ok = t0 < t_end;
-    ar[k].load(gs, t0, ok, tid, C);
+    ar[k].load(gs, t0, ok, lane, C);
     xr[k].load(X, ok ? (uint32_t)(t0 * D * sizeof(E)) : kOOB, tid);
     if (WA) gr[k].load(G, ok ? (uint32_t)(t0 * M * sizeof(E)) : kOOB, tid);
     if (BWD) dr[k].load(Dy, ok ? (uint32_t)(t0 * M * sizeof(E)) : kOOB, tid);
@@ -320,22 +328,32 @@ agg_gated_kernel(const GArgs a, int64_t nagg) {
   fetch(0, t_begin);
   __builtin_amdgcn_sched_barrier(0);  // slot order (the loop's first wait holds on entry too)
   fetch(1, t_begin + C);
-  auto chunk = [&](int k, int64_t t0) {
+  auto chunk = [&](auto kc, int64_t t0) {
+    constexpr int k = decltype(kc)::value, BUF = DB ? k : 0;
+    E *const Xs = Xs_[BUF], *const Vh = Vh_[BUF], *const Vl = Vl_[BUF], *const Ds = Ds_[BUF], *const Bh = Bh_[BUF],
+      *const Bl = Bl_[BUF];
     const int nvalid = t0 < t_end ? (int)(t_end - t0 < C ? t_end - t0 : C) : 0;
-    __syncthreads();
-    ar[k].stage(al, et, nullptr, nvalid, tid, C);
+    // Lane t's retention and step size (1 and 0 past the sequence end and at
+    // a reset, as GateReg::stage), and their products.
+    const bool in = lane < nvalid, cut = ar[k].r != 0;
+    const float av = in ? (cut ? 0.f : ar[k].a) : 1.f, ev = in && !cut ? ar[k].e : 0.f;
+    const float p = wave_scan_mul<false>(av, lane);
+    const float tt = lane_value(p, 63);
+    if constexpr (BWD) {
+      const float pex = dpp_move<kWaveShr1>(p, 1.f);
+      if (lane < C) pw[w][lane] = P * pex;
+    }
+    if constexpr (WA) {
+      const float sex = dpp_move<kWaveShl1>(wave_scan_mul<true>(av, lane), 1.f);
+      if (lane < C) vw[w][lane] = ev * sex;
+    }
+    if constexpr (!DB) __syncthreads();
     xr[k].store(Xs, tid);
     if (BWD) dr[k].store(Ds, tid);
+    if (WA) gr[k].store_scaled(Vh, Vl, tid, vw[w]);
+    if (BWD) dr[k].store_scaled(Bh, Bl, tid, pw[w]);
     __syncthreads();
-    if (w == 0) gate_scan<C>(al, et, pre, suf, pin, sinv, mid, &tot, WA ? vw : nullptr, 1.f, lane);
-    __syncthreads();
-    if (BWD && tid < C) pw[tid] = P * pre[tid];
-    if (WA) gr[k].store_scaled(Vh, Vl, tid, vw);
-    __syncthreads();
-    if (BWD) dr[k].store_scaled(Bh, Bl, tid, pw);
-    const float tt = tot;
     fetch(k, t0 + 2 * C);
-    __syncthreads();
     if (w < IB) {
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb) accA[jb] *= tt;
@@ -367,8 +385,8 @@ agg_gated_kernel(const GArgs a, int64_t nagg) {
     P *= tt;
   };
   for (int64_t t0 = t_begin; t0 < t_end; t0 += 2 * C) {
-    chunk(0, t0);
-    chunk(1, t0 + C);
+    chunk(IntC<0>{}, t0);
+    chunk(IntC<1>{}, t0 + C);
   }
   if (w < IB) {
     // acc[jb] holds A^T[j = 16jb + 4q + r][i = 16w + c]; stored as A[i][j].
