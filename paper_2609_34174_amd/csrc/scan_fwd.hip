@@ -176,7 +176,10 @@ fwd_main_kernel(const KArgs a) {
     auto compute = [&](auto hc) {
     constexpr bool HAS = decltype(hc)::value;
     // Each wave writes its own table (in-order LDS within a wave: no barrier).
-    if constexpr (HAS) didw[w][lane] = __builtin_popcountll(lane == 63 ? dm : dm & ((2ull << lane) - 1));
+    if constexpr (HAS) {
+      didw[w][lane] = __builtin_popcountll(lane == 63 ? dm : dm & ((2ull << lane) - 1));
+      wave_sync();
+    }
 
     // Intra-chunk scores, lower-triangular tiles (tb >= sb) shared by all waves.
     if constexpr (!RS) {

@@ -185,9 +185,10 @@ __device__ __forceinline__ void affine_scan(float& A, float& B, int lane) {
 
 // Decay products of a chunk (C <= 64), computed by one wave: lane t holds
 // alpha_t (1 for lanes >= C).  Product scans, whole chunk and within 16-lane
-// blocks.  Also vw[t] = vsign * eta_t * suf_t when vw != null.
+// blocks.  Also vw[t] = vsign * eta_t * suf_t when vw != null.  Returns the
+// whole product (also in *tot).
 template <int C>
-__device__ __forceinline__ void gate_scan(const float* al, const float* et, float* pre, float* suf,
+__device__ __forceinline__ float gate_scan(const float* al, const float* et, float* pre, float* suf,
                                           float* pin, float* sinv, float* mid, float* tot,
                                           float* vw, float vsign, int lane) {
   constexpr int TB = C / 16;
@@ -218,7 +219,23 @@ __device__ __forceinline__ void gate_scan(const float* al, const float* et, floa
     mid[lane] = m;
   }
   if (lane == 0) *tot = all;
+  return all;
 }
+
+// Gates of a chunk in LDS and the products gate_scan forms of them.  form() is
+// for tables a wave keeps to itself: it takes the gates from the registers of
+// the lane's token, and the wave may read what its lanes wrote.
+template <int C>
+struct __attribute__((aligned(16))) WaveGates {
+  float al[C], et[C], pre[C], suf[C], pin[C], sinv[C], vw[C], mid[16], tot[4];
+  // Returns the chunk's whole decay.
+  __device__ __forceinline__ float form(const GateReg& r, int nvalid, float vsign, int lane) {
+    r.stage(al, et, nullptr, nvalid, lane, C);
+    const float all = gate_scan<C>(al, et, pre, suf, pin, sinv, mid, tot, vw, vsign, lane);
+    wave_sync();
+    return all;
+  }
+};
 
 // F[t][s] for the four (s = 16sb + 4q + r, t = 16tb + c) pairs a lane holds in
 // a score tile; zero where s >= t.
@@ -268,8 +285,8 @@ enum GAggMode { kGAggFwd = 0, kGAggBwd = 1, kGAggBwdSaved = 2 };
 
 // The gates of a chunk are at most 64 tokens, so every wave loads them, one
 // token per lane, and forms their products by itself: the row scales of its
-// share of the staged tiles go through a table of the wave's own (LDS is in
-// order within a wave), and no wave waits for another's scan.  With two
+// share of the staged tiles go through a table of the wave's own, and no wave
+// waits for another's scan.  With two
 // buffers (bf16) a chunk has one barrier; a scan by one wave, published to
 // the others, took four more.
 template <class OP, int D, int M, int C, int MODE>
@@ -347,7 +364,8 @@ agg_gated_kernel(const GArgs a, int64_t nagg) {
       const float sex = dpp_move<kWaveShl1>(wave_scan_mul<true>(av, lane), 1.f);
       if (lane < C) vw[w][lane] = ev * sex;
     }
-    if constexpr (!DB) __syncthreads();
+    if constexpr (DB) wave_sync();
+    else __syncthreads();
     xr[k].store(Xs, tid);
     if (BWD) dr[k].store(Ds, tid);
     if (WA) gr[k].store_scaled(Vh, Vl, tid, vw[w]);
@@ -463,12 +481,20 @@ fwd_gated_kernel(const GArgs a) {
   constexpr int NW = cmax(D, M) / 16, NT = NW * 64;
   constexpr int TB = C / 16, JB = D / 16, IB = M / 16;
   constexpr bool SPL = OP::kSplit == 2;
-  __shared__ E Xs[C * D];
-  __shared__ E Gs[C * M];
-  __shared__ E Vh[C * M];
-  __shared__ E Vl[SPL ? C * M : 1];
-  __shared__ __attribute__((aligned(16))) float al[C], et[C], pre[C], suf[C], pin[C], sinv[C], vw[C];
-  __shared__ float mid[16], tot;
+  // With eight waves (one workgroup to a CU) every wave forms the chunk's gate
+  // products in tables of its own, as in the aggregate pass, and the tiles are
+  // staged in one go, with bf16 into the other of two buffers: one barrier per
+  // chunk instead of four (128 x 128, 16 sequences of 1500: 42.4 -> 37.0 us;
+  // both maps of the 64 -> 128 -> 64 MLP 60 -> 46 us).  With four the scan in
+  // every wave cost more than the barriers (lm-bf16 58.5 -> 61.8 us).
+  constexpr bool PW = NW == 8;
+  constexpr bool DB = SPL && PW && 2 * (C * D + 3 * C * M) * (int)sizeof(E) <= 144 * 1024;
+  constexpr int NB = DB ? 2 : 1;
+  __shared__ E Xs_[NB][C * D];
+  __shared__ E Gs_[NB][C * M];
+  __shared__ E Vh_[NB][C * M];
+  __shared__ E Vl_[NB][SPL ? C * M : 1];
+  __shared__ WaveGates<C> gates[PW ? NW : 1];
   // Y staged through LDS for whole-row stores (16-row x 64-byte tile stores
   // stream to HBM at a fraction of the full-line rate); fp32 [C][M + 4], the
   // pad staggering the owners' tile writes over the banks.
@@ -516,20 +542,30 @@ fwd_gated_kernel(const GArgs a) {
   GateReg ar;
   auto fetch = [&](int64_t t0) {
     const bool ok = t0 < t_end;
-    ar.load(gs, t0, ok, tid, C);
+    ar.load(gs, t0, ok, PW ? lane : tid, C);
     xr.load(X, ok ? (uint32_t)(t0 * D * sizeof(E)) : kOOB, tid);
     gr.load(G, ok ? (uint32_t)(t0 * M * sizeof(E)) : kOOB, tid);
   };
   fetch(t_begin);
-  for (int64_t t0 = t_begin; t0 < t_end; t0 += C) {
+  WaveGates<C>& wg = gates[PW ? w : 0];
+  const float *const al = wg.al, *const et = wg.et, *const pre = wg.pre, *const pin = wg.pin, *const sinv = wg.sinv,
+              *const mid = wg.mid;
+  auto chunk = [&](auto bc, int64_t t0) {
+    constexpr int BUF = DB ? decltype(bc)::value : 0;
+    E *const Xs = Xs_[BUF], *const Gs = Gs_[BUF], *const Vh = Vh_[BUF], *const Vl = Vl_[BUF];
     const int nvalid = (int)(t_end - t0 < C ? t_end - t0 : C);
-    __syncthreads();
-    ar.stage(al, et, nullptr, nvalid, tid, C);
+    float tt = 1.f;
+    if constexpr (PW) tt = wg.form(ar, nvalid, -1.f, lane);
+    if constexpr (!DB) __syncthreads();
+    if constexpr (!PW) ar.stage(wg.al, wg.et, nullptr, nvalid, tid, C);
     xr.store(Xs, tid);
     gr.store(Gs, tid);
+    if constexpr (PW) gr.store_scaled(Vh, Vl, tid, wg.vw);  // -eta_s suf_s g_s, read by the carry
     __syncthreads();
-    if (w == 0) gate_scan<C>(al, et, pre, suf, pin, sinv, mid, &tot, vw, -1.f, lane);
-    __syncthreads();
+    if constexpr (!PW) {
+      if (w == 0) gate_scan<C>(wg.al, wg.et, wg.pre, wg.suf, wg.pin, wg.sinv, wg.mid, wg.tot, wg.vw, -1.f, lane);
+      __syncthreads();
+    }
     if (a.states && w < IB) {
       // Saved for a backward with the same chunk: Delta at this chunk's
       // start, in the order the backward's lanes load it (tiles of rows
@@ -542,7 +578,7 @@ fwd_gated_kernel(const GArgs a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) st[jb * IB * 256 + 4 * (4 * q + r)] = Dt[jb][r];
     }
-    gr.store_scaled(Vh, Vl, tid, vw);  // -eta_s suf_s g_s, read by the carry after a barrier
+    if constexpr (!PW) gr.store_scaled(Vh, Vl, tid, wg.vw);  // read by the carry after a barrier
     fetch(t0 + C);
     if (w < IB) {
       f32x4 acc[TB];
@@ -600,11 +636,14 @@ fwd_gated_kernel(const GArgs a) {
         else buf_store4(Y, (uint32_t)(((t0 + t) * M + 16 * w + 4 * q) * 4), acc[tb]);
       }
     }
-    __syncthreads();
+    if constexpr (!PW) {
+      __syncthreads();
+      tt = wg.tot[0];
+    }
     if constexpr (YSTG) {
       // Whole rows: thread tid stores 16 bytes of row tid / (M/4), so each
       // wave writes four 256-byte rows (rows past T are dropped).  Ys is
-      // rewritten only after the next chunk's third barrier.
+      // rewritten only after the next chunk's staging barrier.
 #pragma unroll
       for (int i = 0; i < C * M / 4 / NT; ++i) {
         const int e = tid + i * NT, r = e / (M / 4), c4 = 4 * (e % (M / 4));
@@ -613,7 +652,6 @@ fwd_gated_kernel(const GArgs a) {
     }
     if (w < IB && t0 + C < t_end) {
       // Carry: Delta^T <- tot Delta^T + X^T V.
-      const float tt = tot;
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb) Dt[jb] *= tt;
 #pragma unroll
@@ -626,6 +664,14 @@ fwd_gated_kernel(const GArgs a) {
           Dt[jb] = mma_split_b<OP>(Dt[jb], OP::load_t(Xs, D, 32 * kb, 16 * jb, lane), vh, vl);
       }
     }
+  };
+  if constexpr (DB) {
+    for (int64_t t0 = t_begin; t0 < t_end; t0 += 2 * C) {
+      chunk(IntC<0>{}, t0);
+      if (t0 + C < t_end) chunk(IntC<1>{}, t0 + C);
+    }
+  } else {
+    for (int64_t t0 = t_begin; t0 < t_end; t0 += C) chunk(IntC<0>{}, t0);
   }
 }
 
