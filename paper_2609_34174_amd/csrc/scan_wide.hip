@@ -519,7 +519,7 @@ static __global__ void __launch_bounds__(256) wide_deta_kernel(const WDetaArgs a
       const float k = live ? x[r] * y[r] : 0.f;
       col[i >> 1][r] += f * k;
       fv[r] = f;
-      kv[r] = cv[r] * k;
+      kv[r] = live ? cv[r] * k : 0.f;  // (a step size nothing reads may be infinite)
     }
     if (a.Km) {
       *reinterpret_cast<f32x4*>(a.Km + o) = kv;

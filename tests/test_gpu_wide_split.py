@@ -29,3 +29,17 @@ def test_wide_split_gate_gradients(dtype, d, m):
         part = gl.scan_bwd_gated(W0, X, G, dY, e, a, r, outputs=subset)
         for k in subset:
             np.testing.assert_array_equal(to_host(part[k]), full[k], err_msg=str(subset))
+
+
+@pytest.mark.parametrize("T", [129, 200])
+def test_wide_unread_step_size(T):
+    """No token reads the last one's write: its step size may be anything."""
+    log(f"wide unread step size T={T}")
+    inp = inputs(1, 1, T, 256, 128, "f32", seed=9, alpha_kind="family", eta_kind="token", with_reset=False)
+    W0, X, G, dY, e, a, r = dev_inputs(inp, "f32")
+    ref = gl.scan_bwd_gated(W0, X, G, dY, e, a, r, outputs=WIDE_BWD)
+    e = e.clone()
+    e[..., -1] = float("inf")
+    got = gl.scan_bwd_gated(W0, X, G, dY, e, a, r, outputs=WIDE_BWD)
+    for k in WIDE_BWD:
+        np.testing.assert_array_equal(to_host(got[k]), to_host(ref[k]), err_msg=k)
