@@ -286,8 +286,12 @@ def _workspace(need, device, workspace):
     if workspace is None:
         return _torch().empty(need, dtype=_torch().uint8, device=device), need
     have = workspace.numel() * workspace.element_size()
+    if not workspace.is_contiguous():  # only what its storage holds from its first element on can be written
+        have = min(have, workspace.untyped_storage().nbytes() - workspace.storage_offset() * workspace.element_size())
     if have < need:
         raise ValueError(f"workspace too small: need {need} bytes")
+    if not workspace.is_cuda:
+        raise ValueError("workspace must be a CUDA/HIP tensor")
     return workspace, have
 
 
@@ -301,17 +305,20 @@ def _out(out, shape, device):
 
 
 def _grads(s, outputs, out, known, device):
-    """The dict of requested backward outputs, those not supplied allocated."""
+    """The dict of requested backward outputs, those not supplied allocated.
+
+    The kernels write every known entry of `out`, requested or not, so each is checked."""
     torch = _torch()
     x, g, t = (s.B, s.H, s.T, s.d_in), (s.B, s.H, s.T, s.d_out), (s.B, s.H, s.T)
     sizes = {"gtilde": x, "dx": x, "dg": g, "deta": t, "dalpha": t, "dw0": (s.H, s.d_out, s.d_in)}
     res = dict(out) if out else {}
+    for k, v in res.items():
+        if k in known and (v is not None or k in outputs):
+            _check_dev(k, v, torch.float32, sizes[k])
     for k in outputs:
         if k not in known:
             raise ValueError(f"unknown output {k!r}")
-        if k in res:
-            _check_dev(k, res[k], torch.float32, sizes[k])
-        else:
+        if k not in res:
             res[k] = torch.empty(sizes[k], dtype=torch.float32, device=device)
     return res
 
