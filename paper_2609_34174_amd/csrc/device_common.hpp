@@ -410,10 +410,12 @@ __device__ __forceinline__ float dpp_move(float src, float fill) {
 __device__ __forceinline__ float lane_value(float v, int l) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
-// Orders a wave's LDS writes before its lanes' later reads of one another's:
-// the hardware keeps a wave's LDS operations in order, the compiler only what
+// Orders a wave's LDS accesses before it against those after it: writes
+// before its lanes' reads of one another's, and reads before the next writes.
+// The hardware keeps a wave's LDS operations in order, the compiler only what
 // it sees of one lane (it may turn a store by some lanes and a load by all
-// into a branch whose loading side runs first).
+// into a branch whose loading side runs first, or move a lane's store ahead of
+// its load where it can tell that lane's two addresses apart).
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();

@@ -228,8 +228,10 @@ __device__ __forceinline__ float gate_scan(const float* al, const float* et, flo
 template <int C>
 struct __attribute__((aligned(16))) WaveGates {
   float al[C], et[C], pre[C], suf[C], pin[C], sinv[C], vw[C], mid[16], tot[4];
-  // Returns the chunk's whole decay.
+  // Returns the chunk's whole decay.  Ordered on both sides: the last chunk's
+  // reads of the tables may still be pending when the next chunk writes them.
   __device__ __forceinline__ float form(const GateReg& r, int nvalid, float vsign, int lane) {
+    wave_sync();
     r.stage(al, et, nullptr, nvalid, lane, C);
     const float all = gate_scan<C>(al, et, pre, suf, pin, sinv, mid, tot, vw, vsign, lane);
     wave_sync();
