@@ -309,29 +309,36 @@ __device__ __forceinline__ int64_t first_reset_in(rsrc_t row, int64_t lo, int64_
 }
 
 // s[i] += (SUB: -=) the aggregates of n segments, the k-th at p(k) + at(i)
-// floats: PU segments' loads are in flight together and added in order.  Past
-// the last one a batch reads it again and adds nothing, so that the loads need
-// no branch.
+// floats, in order, PU segments' loads in flight together.  A whole batch has
+// no branch, the remainder branches around both its loads and its adds: with
+// loads issued for every batch but added behind a branch, the compiler moved
+// each load into its branch, where it is waited for alone (backward of 16
+// sequences of 8192 tokens in 16 segments, 64 x 64 bf16: 70 us, so 57).
 template <int PU, bool SUB, int N, class P, class AT>
 __device__ __forceinline__ void sum_segments(f32x4 (&s)[N], int n, P p, AT at) {
-  for (int k = 0; k < n; k += PU) {
+  auto batch = [&](int k, auto full) {
+    constexpr bool FULL = decltype(full)::value != 0;
     f32x4 v[PU][N];
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
-      const float* b = p(k + u < n ? k + u : n - 1);
+      if (!FULL && k + u >= n) break;
+      const float* b = p(k + u);
 #pragma unroll
       for (int i = 0; i < N; ++i) v[u][i] = *reinterpret_cast<const f32x4*>(b + at(i));
     }
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
-      if (k + u >= n) break;
+      if (!FULL && k + u >= n) break;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         if constexpr (SUB) s[i] -= v[u][i];
         else s[i] += v[u][i];
       }
     }
-  }
+  };
+  int k = 0;
+  for (; k + PU <= n; k += PU) batch(k, IntC<1>{});
+  if (k < n) batch(k, IntC<0>{});
 }
 
 // ---------------------------------------------------------------------------
