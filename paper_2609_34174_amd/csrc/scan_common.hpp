@@ -407,12 +407,15 @@ agg_kernel(const KArgs a, int64_t nagg) {
   // against four; one, three, six and eight were slower, and so were two
   // groups of waves per workgroup): more loads in flight per CU only add
   // concurrent streams.  The register sets are used in turn.  A segment of an
-  // odd number of chunks ends with a step of its own (ODD) where a chunk
-  // costs most, with fp32 tiles and with per-token eta (backward pass of 36
-  // sequences of T = 1999: 14.0 -> 12.2 us); elsewhere it runs the second
-  // set's step on zero tiles, as the extra copy of the step cost the even
-  // segments 0.4 us (1 us with resets).
-  constexpr int DEPTH = 2;
+  // odd number of chunks ends with a step of its own (ODD) with per-token eta
+  // (backward pass of 36 sequences of T = 1999: 14.0 -> 12.2 us); elsewhere it
+  // runs the second set's step on zero tiles, as the extra copy of the step
+  // cost the even segments 0.4 us (1 us with resets).  fp32 without resets
+  // stages one chunk ahead: its tiles take twice the registers, its matrix
+  // steps eight times as long (backward pass of 128 sequences of 500, 128 x
+  // 128: 62 us with two sets, 44 us with one; 128 x 64 49 -> 27 us; 64 x 64
+  // 18.5 -> 19 us with more than one chunk, 9.0 -> 8.7 us with one).
+  constexpr int DEPTH = OP::kSplit == 2 || RST ? 2 : 1;
   Tile4<OP, C, D, NT> xr[DEPTH];
   Tile4<OP, C, M, NT> gr[DEPTH], dr[DEPTH];
   EtaReg<ETAV> er[DEPTH];
@@ -496,14 +499,17 @@ agg_kernel(const KArgs a, int64_t nagg) {
       }
     }
   };
-  static_assert(DEPTH == 2, "the walk below takes chunks in pairs");
-  constexpr bool ODD = !RST && (ETAV || OP::kSplit == 1);
   int64_t t0 = t_begin;
-  for (; t0 + (ODD ? C : 0) < t_end; t0 += 2 * C) {
-    chunk(IntC<0>{}, t0);
-    chunk(IntC<1>{}, t0 + C);
+  if constexpr (DEPTH == 2) {
+    constexpr bool ODD = !RST && ETAV;
+    for (; t0 + (ODD ? C : 0) < t_end; t0 += 2 * C) {
+      chunk(IntC<0>{}, t0);
+      chunk(IntC<1>{}, t0 + C);
+    }
+    if (ODD && t0 < t_end) chunk(IntC<0>{}, t0);
+  } else {
+    for (; t0 < t_end; t0 += C) chunk(IntC<0>{}, t0);
   }
-  if (ODD && t0 < t_end) chunk(IntC<0>{}, t0);
   if (w < IB) {
     // accA[jb] holds A^T[j = 16jb + 4q + r][i = 16w + c].
     const int64_t base = (bh * a.nseg + seg) * M * D;

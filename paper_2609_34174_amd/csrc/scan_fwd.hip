@@ -75,7 +75,12 @@ fwd_main_kernel(const KArgs a) {
   const rsrc_t Cst = make_rsrc(RST && a.cstate ? a.cstate + bh * nchs * M * D : nullptr,
                                RST && a.cstate ? (uint32_t)(nchs * M * D * 4) : 0u);
 
-  // Register staging, two chunks ahead.
+  // Register staging: two chunks ahead with bf16, in two register sets.  fp32 tiles take
+  // twice the registers and a chunk's matrix steps eight times as long, which
+  // covers the loads of one (main kernel of 128 sequences of 500, 128 x 64:
+  // 108 us with two sets and 127 spilled registers, 64 us so; 128 x 128 with
+  // per-token eta 65 -> 53 us; with resets, 64 x 64, 39 -> 28 us).
+  constexpr int DEPTH = OP::kSplit == 2 ? 2 : 1;
   Tile4<OP, C, D, NT> xa, xb;
   Tile4<OP, C, M, NT> ga, gb;
   EtaReg<ETAV> ea, eb;
@@ -94,7 +99,7 @@ fwd_main_kernel(const KArgs a) {
   // start at or before t_begin: W_0 if that is t_begin itself, else W_0 minus
   // the (post-reset) aggregates from that document's segment on.
   fetch(xa, ga, ea, ra, t_begin);
-  fetch(xb, gb, eb, rb, t_begin + C);
+  if constexpr (DEPTH == 2) fetch(xb, gb, eb, rb, t_begin + C);
   int64_t j_first = 0;
   bool from_w0 = false;
   if constexpr (RST) {
@@ -170,7 +175,7 @@ fwd_main_kernel(const KArgs a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) buf_store1(Cst, o + (uint32_t)((16 * jb + 4 * q + r) * M * 4), Ws[jb][r]);
     }
-    fetch(xr, gr, er, rr, t0 + 2 * C);
+    fetch(xr, gr, er, rr, t0 + DEPTH * C);
     // The chunk's compute, compiled with the reset masks (HAS) for the chunks
     // that hold a reset and without them for the others.
     auto compute = [&](auto hc) {
@@ -346,16 +351,23 @@ fwd_main_kernel(const KArgs a) {
     else compute(IntC<0>{});
   };
 
-  // The two register sets in turn, then the last chunk of a segment of an odd
-  // number of them (a zero step in the second set's place cost a whole
-  // chunk's time; leaving the loop between the two steps instead cost the
-  // long segments the overlap of their loads: 37.7 -> 40.3 us at lm-bf16).
+  // The last chunk of a segment is a copy of its own.  bf16: after the two
+  // register sets in turn, where their number is odd (a zero step in the
+  // second set's place cost a whole chunk's time; leaving the loop between the
+  // two steps instead cost the long segments the overlap of their loads:
+  // 37.7 -> 40.3 us at lm-bf16).  fp32: always, which spares a segment of one
+  // chunk the loop (8 sequences of 1000, 128 x 64: 26.2 -> 23.6 us).
   int64_t t0 = t_begin;
-  for (; t0 + C < t_end; t0 += 2 * C) {
-    chunk(xa, ga, ea, ra, t0, IntC<0>{});
-    chunk(xb, gb, eb, rb, t0 + C, IntC<1>{});
+  if constexpr (DEPTH == 2) {
+    for (; t0 + C < t_end; t0 += 2 * C) {
+      chunk(xa, ga, ea, ra, t0, IntC<0>{});
+      chunk(xb, gb, eb, rb, t0 + C, IntC<1>{});
+    }
+    if (t0 < t_end) chunk(xa, ga, ea, ra, t0, IntC<0>{});
+  } else {
+    for (; t0 + C < t_end; t0 += C) chunk(xa, ga, ea, ra, t0, IntC<0>{});
+    chunk(xa, ga, ea, ra, t0, IntC<1>{});
   }
-  if (t0 < t_end) chunk(xa, ga, ea, ra, t0, IntC<0>{});
 }
 
 // ---------------------------------------------------------------------------
