@@ -87,7 +87,7 @@ void layout_ws(Plan* out, int64_t BH, size_t md) {
   out->ws_bwd = out->off_rfin + round_up((size_t)BH * md, 256);
 }
 
-int make_plan(const gradlev_shape* s, Plan* out) {
+int make_plan(const gradlev_shape* s, Plan* out, bool reset = false) {
   if (!s || !out) return GRADLEV_ERR_INVALID;
   if (s->B < 1 || s->H < 1 || s->T < 1 || s->d_in < 1 || s->d_out < 1) return GRADLEV_ERR_INVALID;
   if (s->in_dtype != GRADLEV_F32 && s->in_dtype != GRADLEV_BF16) return GRADLEV_ERR_INVALID;
@@ -119,14 +119,14 @@ int make_plan(const gradlev_shape* s, Plan* out) {
 
   out->fwd = base;
   out->fwd.chunk = fwd_chunk_for(bf, d, m, (int)s->chunk);
-  int64_t sc = pick_seg_chunks(BH, s->T, out->fwd.chunk, md, fwd_seg_cost(bf, d, m), s->segment);
+  int64_t sc = pick_seg_chunks(BH, s->T, out->fwd.chunk, md, fwd_seg_cost(bf, d, m, reset), s->segment);
   out->fwd.seg_len = sc * out->fwd.chunk;
   out->fwd.nseg = (s->T + out->fwd.seg_len - 1) / out->fwd.seg_len;
   if (out->fwd.nseg > 16) return GRADLEV_ERR_UNSUPPORTED;
 
   out->bwd = base;
   out->bwd.chunk = bwd_chunk_for(bf, d, m, (int)s->chunk);
-  sc = pick_seg_chunks(BH, s->T, out->bwd.chunk, md, bwd_seg_cost(bf, d, m), s->segment);
+  sc = pick_seg_chunks(BH, s->T, out->bwd.chunk, md, bwd_seg_cost(bf, d, m, reset), s->segment);
   out->bwd.seg_len = sc * out->bwd.chunk;
   out->bwd.nseg = (s->T + out->bwd.seg_len - 1) / out->bwd.seg_len;
   if (out->bwd.nseg > 16) return GRADLEV_ERR_UNSUPPORTED;
@@ -143,8 +143,8 @@ int make_plan(const gradlev_shape* s, Plan* out) {
 // so that no forward tile straddles a saved boundary (the backward tile, 32
 // or 64 tokens, divides the forward's, 64 or 128); the forward's segments
 // are rounded up to whole backward segments.
-int make_saved_plan(const gradlev_shape* s, Plan* out, size_t* saved_bytes) {
-  const int rc = make_plan(s, out);
+int make_saved_plan(const gradlev_shape* s, Plan* out, size_t* saved_bytes, bool reset = false) {
+  const int rc = make_plan(s, out, reset);
   if (rc != GRADLEV_OK) return rc;
   const int64_t fc = out->fwd.chunk;
   const int64_t sb = (out->bwd.seg_len + fc - 1) / fc * fc;
@@ -182,7 +182,7 @@ int make_reset_plan(const gradlev_shape* s, ResetPlan* out) {
   gradlev_shape s64 = *s;
   s64.chunk = 64;
   size_t sv = 0;
-  const int rc = make_saved_plan(&s64, &out->p, &sv);
+  const int rc = make_saved_plan(&s64, &out->p, &sv, true);
   if (rc != GRADLEV_OK) return rc;
   if (out->p.fwd.chunk != 64 || out->p.bwd.chunk != 64) return GRADLEV_ERR_UNSUPPORTED;
   const int64_t BH = s->B * s->H;

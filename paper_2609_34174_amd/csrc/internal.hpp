@@ -120,9 +120,10 @@ hipError_t launch_scan_bwd_gated(const ScanProblem& p, const GatedPtrs& a, hipSt
 // Tile lengths each kernel family supports for a shape (LDS budget).
 int fwd_chunk_for(int bf16, int d, int m, int requested);
 int bwd_chunk_for(int bf16, int d, int m, int requested);
-// Time of a pass by its segmentation, for the planner.
-SegCost fwd_seg_cost(int bf16, int d, int m);
-SegCost bwd_seg_cost(int bf16, int d, int m);
+// Time of a pass by its segmentation, for the planner; `reset`: of the reset
+// pair's passes (64 x 64 maps).
+SegCost fwd_seg_cost(int bf16, int d, int m, bool reset = false);
+SegCost bwd_seg_cost(int bf16, int d, int m, bool reset = false);
 
 // Wide maps (parallel form, scan_wide.hip): d and m multiples of 128, at
 // least one above 128; exclusive reads.  fmode: 0 no retention or resets

@@ -1101,8 +1101,9 @@ static_assert(lds_bytes_bwd(0, 64, 64, 64, 1) <= 160 * 1024, "fp32 backward tile
 static_assert(lds_bytes_bwd(0, 128, 128, 32, 1) <= 160 * 1024, "fp32 backward tile does not fit LDS");
 
 // Fitted as the forward's (fwd_seg_cost), to the plain call with every output.
-SegCost bwd_seg_cost(int bf16, int d, int m) {
+SegCost bwd_seg_cost(int bf16, int d, int m, bool reset) {
   const int wide = (d == 128) + (m == 128);
+  if (bf16 && reset) return {11.0f, 9.4f, 0.41f, 12.0f, 0.25f, 5.9f, 2, 1.43f};
   static const SegCost bf[3] = {{5.2f, 4.8f, 0.36f, 7.6f, 0.81f, 4.9f, 2, 1.49f},
                                 {2.f, 1.6f, 0.74f, 10.2f, 0.83f, 8.6f, 1, 0.f},
                                 {6.4f, 5.4f, 0.7f, 8.2f, 1.94f, 10.3f, 1, 0.f}};

@@ -1,6 +1,7 @@
 """The planner's segmentation without a hint (host only): whole chunks, at most
-16 segments, no empty segment, and aggregates that outgrow the static scratch
-only where a single segment per sequence already does."""
+16 segments, no empty segment, aggregates that outgrow the static scratch only
+where a single segment per sequence already does, and the reset pair's choices
+beside measured times."""
 
 import pytest
 
@@ -18,3 +19,26 @@ def test_automatic_segments(dtype, d, m, BH):
             assert seg % C == 0 and 1 <= n <= 16 and (n - 1) * seg < T <= n * seg
         one = 3 * BH * d * m * 4  # aggregates of one segment per sequence, and dW0's sums
         assert p.workspace_bytes <= max(gl.STATIC_SCRATCH_BYTES, one) + 3 * 256
+
+
+# Forward + backward of the bf16 reset pair, us by segments per sequence (64 x 64,
+# scalar eta, documents of mean length 200), measured on an MI355X.
+RESET_US = {
+    (1, 2000): {4: 107, 5: 94, 6: 89, 8: 71, 11: 62, 16: 54},
+    (8, 2000): {4: 108, 5: 96, 6: 90, 8: 73, 11: 64, 16: 57},
+    (16, 2000): {4: 110, 5: 97, 6: 91, 8: 75, 11: 66, 16: 63},
+    (24, 4000): {4: 184, 5: 165, 6: 144, 8: 119, 11: 104, 16: 102},
+    (40, 2000): {4: 114, 5: 107, 6: 99, 8: 94, 11: 91, 16: 103},
+    (40, 4000): {4: 191, 5: 162, 6: 147, 8: 147, 11: 126, 16: 143},
+    (64, 1000): {2: 116, 3: 97, 4: 81, 6: 89, 8: 79, 16: 111},
+    (128, 2000): {2: 196, 3: 186, 4: 160, 5: 193, 6: 196, 8: 179, 11: 201, 16: 221},
+}
+
+
+@pytest.mark.parametrize("BH,T", sorted(RESET_US))
+def test_reset_pair_segments(BH, T):
+    """The backward's count, from the saved buffer's size: segment-end weights and chunk-start states."""
+    saved, _ = gl.reset_saved_bytes(gl.make_shape(B=BH, H=1, T=T, d_in=64, d_out=64, dtype=gl.BF16))
+    n = saved // (BH * 64 * 64 * 4) - (T + 63) // 64
+    us = RESET_US[BH, T]
+    assert us.get(n, 1e9) <= 1.05 * min(us.values()), (n, us)
