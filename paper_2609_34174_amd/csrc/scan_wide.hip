@@ -689,7 +689,7 @@ static __global__ void __launch_bounds__(256) wide_dalpha_kernel(const WDetaArgs
 // sees W_0 undiscounted).  Tile 128 (i over d_out) x 128 (j over d_in) per
 // head; the contraction runs over the batch rows and tokens in a fixed order,
 // 64 tokens per step, both operands read transposed from row-major token
-// tiles.  Wave (wj, wi) owns a 64 x 64 block D[j][i] (a lane holds 4
+// tiles, by one group of four waves or by the pipeline's two.  Wave (wj, wi) owns a 64 x 64 block D[j][i] (a lane holds 4
 // consecutive j of one i: 16-byte stores into the row-major dW0).
 // ---------------------------------------------------------------------------
 struct WDw0Args {
@@ -699,13 +699,14 @@ struct WDw0Args {
   int64_t B, H, T, d, m;
 };
 
-template <class OP>
-static __global__ void __launch_bounds__(512) wide_dw0_kernel(const WDw0Args a) {
+template <class OP, int GROUPS>
+static __global__ void __launch_bounds__(256 * GROUPS) wide_dw0_kernel(const WDw0Args a) {
   typedef typename OP::elem E;
   typedef typename OP::frag F;
-  constexpr int BT = 64, BN = 128, NT = 512, TILE = BT * BN;
+  constexpr int BT = 64, BN = 128, NT = 256 * GROUPS, TILE = BT * BN;
   constexpr int PR = BN * BN * 4 / (int)sizeof(E);  // group 1's accumulators: the fp32 tile
-  __shared__ __attribute__((aligned(16))) E lds[4 * TILE > PR ? 4 * TILE : PR];  // two buffers of X [t][j] | dY [t][i]
+  // Buffers of X [t][j] | dY [t][i].
+  __shared__ __attribute__((aligned(16))) E lds[GROUPS == 1 ? 2 * TILE : 4 * TILE > PR ? 4 * TILE : PR];
   const int64_t nJ = a.d / BN, nI = a.m / BN;
   const int64_t h = blockIdx.x / (nI * nJ), rest = blockIdx.x % (nI * nJ);
   const int64_t i0 = BN * (rest / nJ), j0 = BN * (rest % nJ);
@@ -732,27 +733,51 @@ static __global__ void __launch_bounds__(512) wide_dw0_kernel(const WDw0Args a) 
     x.xt.load(Xr, ok ? (uint32_t)(t0 * a.d * es) : kOOB, (uint32_t)(a.d * es), (uint32_t)(j0 * es), tid);
     x.dt.load(Dr, ok ? (uint32_t)(t0 * a.m * es) : kOOB, (uint32_t)(a.m * es), (uint32_t)(i0 * es), tid);
   };
-  auto store = [&](Set& x, auto buf) {
-    E* const L = lds + decltype(buf)::value * 2 * TILE;
-    x.xt.store(L, tid);
-    x.dt.store(L + TILE, tid);
-  };
-  F xf[4], df[4];
-  auto load = [&](auto buf) {
-    const E* const L = lds + decltype(buf)::value * 2 * TILE;
+  if constexpr (GROUPS == 1) {
+    Set x;
+    fetch(x, 0);
+    for (int64_t k = 0; k < n; ++k) {
+      __syncthreads();
+      x.xt.store(lds, tid);
+      x.dt.store(lds + TILE, tid);
+      __syncthreads();
+      fetch(x, k + 1);
 #pragma unroll
-    for (int y = 0; y < 4; ++y) df[y] = OP::load_t(L + TILE, BN, 32 * kh, 64 * wi + 16 * y, lane);
+      for (int kk = 0; kk < BT; kk += 32) {
+        F df[4];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) xf[x] = OP::load_t(L, BN, 32 * kh, 64 * wj + 16 * x, lane);
-  };
-  auto mma = [&]() {
+        for (int y = 0; y < 4; ++y) df[y] = OP::load_t(lds + TILE, BN, kk, 64 * wi + 16 * y, lane);
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+        for (int x4 = 0; x4 < 4; ++x4) {
+          const F xf = OP::load_t(lds, BN, kk, 64 * wj + 16 * x4, lane);
 #pragma unroll
-      for (int y = 0; y < 4; ++y) acc[x][y] = OP::mma(acc[x][y], xf[x], df[y]);
-  };
-  pipeline<Set>(n, fetch, store, load, mma);
-  if (!add_groups(acc, lds, kh, w & 3, lane)) return;
+          for (int y = 0; y < 4; ++y) acc[x4][y] = OP::mma(acc[x4][y], xf, df[y]);
+        }
+      }
+    }
+  } else {
+    auto store = [&](Set& x, auto buf) {
+      E* const L = lds + decltype(buf)::value * 2 * TILE;
+      x.xt.store(L, tid);
+      x.dt.store(L + TILE, tid);
+    };
+    F xf[4], df[4];
+    auto load = [&](auto buf) {
+      const E* const L = lds + decltype(buf)::value * 2 * TILE;
+#pragma unroll
+      for (int y = 0; y < 4; ++y) df[y] = OP::load_t(L + TILE, BN, 32 * kh, 64 * wi + 16 * y, lane);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) xf[x] = OP::load_t(L, BN, 32 * kh, 64 * wj + 16 * x, lane);
+    };
+    auto mma = [&]() {
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) acc[x][y] = OP::mma(acc[x][y], xf[x], df[y]);
+    };
+    pipeline<Set>(n, fetch, store, load, mma);
+    if (!add_groups(acc, lds, kh, w & 3, lane)) return;
+  }
   // Lane (c, q) of block (x, y): j = j0 + 64 wj + 16 x + 4 q + r, i = i0 + 64 wi + 16 y + c.
 #pragma unroll
   for (int y = 0; y < 4; ++y) {
@@ -1179,7 +1204,18 @@ static hipError_t wide_bwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
   if (f.dW0) {
     WDw0Args wa{f.X, f.dY, f.dW0, p.B, p.H, p.T, p.d, p.m};
     timing_begin(GRADLEV_K_WIDE_OUT, s);
-    hipLaunchKernelGGL((wide_dw0_kernel<OP>), dim3((unsigned)(p.H * (p.m / 128) * (p.d / 128))), dim3(512), 0, s, wa);
+    const unsigned tiles = (unsigned)(p.H * (p.m / 128) * (p.d / 128));
+    // Eight waves with two buffers while every CU has at most one tile and the
+    // walk is long (bf16, 256 tiles of 32 steps 52 -> 44 us, of 8 the same, of 4
+    // 16.4 -> 17.5); more tiles run beside one another with four waves (512 tiles
+    // of 32 steps 62 us against 75), and fp32 spills with eight (256 tiles of 32
+    // steps 169 us against 192, of one 20 against 32; 16 of 32 161 against 159).
+    if (OP::kSplit == 2 && tiles <= 256 && p.B * ((p.T + 63) / 64) >= 16) {
+      if constexpr (OP::kSplit == 2)
+        hipLaunchKernelGGL((wide_dw0_kernel<OP, 2>), dim3(tiles), dim3(512), 0, s, wa);
+    } else {
+      hipLaunchKernelGGL((wide_dw0_kernel<OP, 1>), dim3(tiles), dim3(256), 0, s, wa);
+    }
     timing_end(GRADLEV_K_WIDE_OUT, s);
   }
   return hipGetLastError();
