@@ -199,32 +199,42 @@ struct GTile {
 // other set's loads, on entry too.  Steps run in pairs: one past n stages
 // zeros (its requests lie past the buffers) and adds nothing; skipping it by a
 // branch moved the accumulators to and fro (score kernel 27 -> 40 us).
-template <class SET, class FETCH, class STORE, class LOAD, class MMA>
-__device__ __forceinline__ void pipeline(int64_t n, FETCH fetch, STORE store, LOAD load, MMA mma) {
+// DB false: a single buffer and two barriers a step, in half the LDS and fewer
+// registers; where that is the better one, wide_out says.
+template <class SET, bool DB, class FETCH, class STORE, class STEP>
+__device__ __forceinline__ void pipeline(int64_t n, FETCH fetch, STORE store, STEP step) {
   SET s0, s1;
-  fetch(s0, 0);
-  __builtin_amdgcn_sched_barrier(0);
-  fetch(s1, 1);
-  __builtin_amdgcn_sched_barrier(0);
-  store(s0, IntC<0>{});
-  fetch(s0, 2);
-  __syncthreads();
-  auto next = [&]() {
+  auto sync = [&]() {
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
   };
-  for (int64_t k = 0; k < n; k += 2) {
-    load(IntC<0>{});
-    mma();
-    store(s1, IntC<1>{});
-    fetch(s1, k + 3);
-    next();
-    load(IntC<1>{});
-    mma();
+  fetch(s0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  fetch(s1, 1);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (DB) {
     store(s0, IntC<0>{});
-    fetch(s0, k + 4);
-    next();
+    fetch(s0, 2);
+    __syncthreads();
+  }
+  auto turn = [&](SET& s, int64_t k, auto buf, auto other) {
+    if constexpr (DB) {  // s holds step k + 1's tiles
+      step(buf);
+      store(s, other);
+      fetch(s, k + 3);
+      sync();
+    } else {  // step k's
+      sync();
+      store(s, IntC<0>{});
+      __syncthreads();
+      fetch(s, k + 2);
+      step(IntC<0>{});
+    }
+  };
+  for (int64_t k = 0; k < n; k += 2) {
+    turn(DB ? s1 : s0, k, IntC<0>{}, IntC<1>{});
+    turn(DB ? s0 : s1, k + 1, IntC<1>{}, IntC<0>{});
   }
 }
 
@@ -761,21 +771,19 @@ static __global__ void __launch_bounds__(256 * GROUPS) wide_dw0_kernel(const WDw
       x.xt.store(L, tid);
       x.dt.store(L + TILE, tid);
     };
-    F xf[4], df[4];
-    auto load = [&](auto buf) {
+    auto step = [&](auto buf) {
       const E* const L = lds + decltype(buf)::value * 2 * TILE;
+      F xf[4], df[4];
 #pragma unroll
       for (int y = 0; y < 4; ++y) df[y] = OP::load_t(L + TILE, BN, 32 * kh, 64 * wi + 16 * y, lane);
 #pragma unroll
       for (int x = 0; x < 4; ++x) xf[x] = OP::load_t(L, BN, 32 * kh, 64 * wj + 16 * x, lane);
-    };
-    auto mma = [&]() {
 #pragma unroll
       for (int x = 0; x < 4; ++x)
 #pragma unroll
         for (int y = 0; y < 4; ++y) acc[x][y] = OP::mma(acc[x][y], xf[x], df[y]);
     };
-    pipeline<Set>(n, fetch, store, load, mma);
+    pipeline<Set, true>(n, fetch, store, step);
     if (!add_groups(acc, lds, kh, w & 3, lane)) return;
   }
   // Lane (c, q) of block (x, y): j = j0 + 64 wj + 16 x + 4 q + r, i = i0 + 64 wi + 16 y + c.
@@ -805,7 +813,7 @@ struct WOutArgs {
 // forward's scores and V = dY it is dG, with the read's scores and V = X the
 // write side of dX (the transposed contraction of the same score matrix, read
 // from its stored lower triangle with transposing LDS reads).
-template <class OP, bool TRANS, int BN, int MODE>
+template <class OP, bool TRANS, int BN, int MODE, bool DB>
 static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) {
   typedef typename OP::elem E;
   typedef typename OP::frag F;
@@ -816,7 +824,8 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
   constexpr int PR = BM * BN * 4 / (int)sizeof(E);  // the kh = 1 waves' accumulators: a BM x BN fp32 partial
   static_assert(4 * NB * 4 * 64 * 16 == BM * BN * 4, "reduction layout covers the tile once");
   constexpr int PM = P1 > P2 ? P1 : P2;
-  __shared__ __attribute__((aligned(16))) E lds[2 * PM > PR ? 2 * PM : PR];  // two step buffers of PM
+  constexpr int NBUF = DB ? 2 : 1;
+  __shared__ __attribute__((aligned(16))) E lds[NBUF * PM > PR ? NBUF * PM : PR];  // step buffers of PM
   // Phase 1: Qs | Ph | Pl.  Phase 2: Shs | Sls | Vs (fp32: Qs | Ph and Shs | Vs).
 
   const int64_t nTB = a.Tp / BM, nNB = a.wout / BN;
@@ -824,7 +833,7 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
   const int64_t tb = MODE == 0 ? nTB - 1 - L / per_row : L / per_row;  // heaviest row tiles first
   const int64_t bh = (L % per_row) / nNB, nb = L % nNB;
   const int64_t h = bh % a.H;
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, w = DB ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const int kh = w >> 2, wt = (w >> 1) & 1, wn = w & 1;
   const int c = lane & 15, q = lane >> 4;
   const int64_t t0 = BM * tb, n0 = BN * nb;
@@ -870,15 +879,14 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
       x.qt.store(L, tid);
       x.wt.template store_split<OP>(L + TILE, L + TILE + (SPLIT ? PT : 0), tid);
     };
-    F qf[4], ph[NB], pl[SPLIT ? NB : 1];
-    auto load = [&](auto buf) {
+    auto step = [&](auto buf) {
       const E* const Qs = lds + decltype(buf)::value * PM;
       const E* const Ph = Qs + TILE;
       const int kk = 32 * kh;
+      F qf[4], ph[NB], pl[SPLIT ? NB : 1];
 #pragma unroll
       for (int j = 0; j < 4; ++j) qf[j] = OP::load_n_sep(Qs, BK, 64 * wt + 16 * j, kk, lane);
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
+      auto load = [&](int i) {
         if constexpr (TRANS) {
           ph[i] = OP::load_t(Ph, BN, kk, BN / 2 * wn + 16 * i, lane);
           if constexpr (SPLIT) pl[i] = OP::load_t(Ph + PT, BN, kk, BN / 2 * wn + 16 * i, lane);
@@ -886,15 +894,18 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
           ph[i] = OP::load_n_sep(Ph, BK, BN / 2 * wn + 16 * i, kk, lane);
           if constexpr (SPLIT) pl[i] = OP::load_n_sep(Ph + PT, BK, BN / 2 * wn + 16 * i, kk, lane);
         }
-      }
-    };
-    auto mma = [&]() {
+      };
+      if constexpr (DB)
 #pragma unroll
-      for (int i = 0; i < NB; ++i)
+        for (int i = 0; i < NB; ++i) load(i);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if constexpr (!DB) load(i);
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = mma_split_a<OP>(acc[i][j], ph[i], pl[SPLIT ? i : 0], qf[j]);
+      }
     };
-    pipeline<Set>(n1, fetch, store, load, mma);
+    pipeline<Set, DB>(n1, fetch, store, step);
   }
 
   // Phase 2: acc += S V over s in [0, 128 (tb + 1)) (causal), or
@@ -928,11 +939,11 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
       if constexpr (SPLIT) x.sl.store(L + TILE, tid);
       x.vt.store(L + (SPLIT ? 2 : 1) * TILE, tid);
     };
-    F sfh[4], sfl[SPLIT ? 4 : 1], vf[NB];
-    auto load = [&](auto buf) {
+    auto step = [&](auto buf) {
       const E* const Shs = lds + decltype(buf)::value * PM;
       const E* const Vs = Shs + (SPLIT ? 2 : 1) * TILE;
       const int kk = 32 * kh;
+      F sfh[4], sfl[SPLIT ? 4 : 1], vf[NB];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if constexpr (MODE == 0) {
@@ -943,16 +954,18 @@ static __global__ void __launch_bounds__(512) wide_out_kernel(const WOutArgs a) 
           if constexpr (SPLIT) sfl[j] = OP::load_t(Shs + TILE, BM, kk, 64 * wt + 16 * j, lane);
         }
       }
+      auto load = [&](int i) { vf[i] = OP::load_t(Vs, BN, kk, BN / 2 * wn + 16 * i, lane); };
+      if constexpr (DB)
 #pragma unroll
-      for (int i = 0; i < NB; ++i) vf[i] = OP::load_t(Vs, BN, kk, BN / 2 * wn + 16 * i, lane);
-    };
-    auto mma = [&]() {
+        for (int i = 0; i < NB; ++i) load(i);
 #pragma unroll
-      for (int i = 0; i < NB; ++i)
+      for (int i = 0; i < NB; ++i) {
+        if constexpr (!DB) load(i);
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = mma_split_b<OP>(acc[i][j], vf[i], sfh[j], sfl[SPLIT ? j : 0]);
+      }
     };
-    pipeline<Set>(n2, fetch, store, load, mma);
+    pipeline<Set, DB>(n2, fetch, store, step);
   }
 
   if (!add_groups(acc, lds, kh, w & 3, lane)) return;
@@ -1106,13 +1119,29 @@ void wide_out(const WideProblem& p, const WidePtrs& f, const WideWs& ws, int mod
   const int64_t t128 = BH * (p.Tp / 128) * (wout / 128);
   const bool narrow = t128 < 2 * 256;
   const unsigned g = (unsigned)(narrow ? 2 * t128 : t128);
+  constexpr bool BF = OP::kSplit == 2;
+  auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(g), dim3(512), 0, s, oa); };
+  // Double-buffered steps but for two kinds.  fp32 128-wide tiles whose V or W_0
+  // fragments are read transposed spill with two buffers' addresses (read of 16
+  // sequences of 512, 1024 -> 4096: 852 us, so 587).  The anti-causal mode has no
+  // W_0 phase, so its walks are short, and with one buffer a second workgroup
+  // hides a bf16 walk's start and end (dG of 16 sequences of 512, 1024 -> 4096:
+  // 110 -> 80 us; 2 of 1024 37.3 -> 33.7) unless the grid leaves most CUs one
+  // workgroup, or few more with long walks (1 of 3072, 512 -> 512: 42.5 us
+  // against 51; 1 of 2048, 512 -> 2048 34.7 against 36.2).
   if (mode == 1) {
-    if (narrow) hipLaunchKernelGGL((wide_out_kernel<OP, false, 64, 1>), dim3(g), dim3(512), 0, s, oa);
-    else hipLaunchKernelGGL((wide_out_kernel<OP, false, 128, 1>), dim3(g), dim3(512), 0, s, oa);
-  } else if (trans && narrow) hipLaunchKernelGGL((wide_out_kernel<OP, true, 64, 0>), dim3(g), dim3(512), 0, s, oa);
-  else if (trans) hipLaunchKernelGGL((wide_out_kernel<OP, true, 128, 0>), dim3(g), dim3(512), 0, s, oa);
-  else if (narrow) hipLaunchKernelGGL((wide_out_kernel<OP, false, 64, 0>), dim3(g), dim3(512), 0, s, oa);
-  else hipLaunchKernelGGL((wide_out_kernel<OP, false, 128, 0>), dim3(g), dim3(512), 0, s, oa);
+    if constexpr (BF) {
+      if (narrow && (g <= 256 || (g <= 512 && p.Tp >= 12 * 128))) return run(wide_out_kernel<OP, false, 64, 1, true>);
+    }
+    if (narrow) run(wide_out_kernel<OP, false, 64, 1, false>);
+    else run(wide_out_kernel<OP, false, 128, 1, false>);
+  } else if (trans) {
+    if (narrow) run(wide_out_kernel<OP, true, 64, 0, true>);
+    else run(wide_out_kernel<OP, true, 128, 0, BF>);
+  } else {
+    if (narrow) run(wide_out_kernel<OP, false, 64, 0, true>);
+    else run(wide_out_kernel<OP, false, 128, 0, true>);
+  }
 }
 
 // Forward (read = false: Q = K = X, V = G) or transpose read (read = true:

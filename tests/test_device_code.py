@@ -36,7 +36,7 @@ def test_segment_sums_keep_their_loads_in_flight(kernel):
     assert {k: n for k, n in found.items() if n >= 4} == {}
 
 
-@pytest.mark.parametrize("kernel", ["agg_kernel<OpF32", "fwd_main_kernel<OpF32, 128, 128", "wide_dw0_kernel"])
+@pytest.mark.parametrize("kernel", ["agg_kernel<OpF32", "fwd_main_kernel<OpF32, 128, 128", "wide_"])
 def test_streaming_kernels_do_not_spill(kernel):
     """fp32 tiles take twice bf16's registers: a second set of them, or a second
     buffer's addresses, has spilled up to 67 registers in these loops."""
