@@ -480,6 +480,10 @@ struct WDetaArgs {
   int KS;
   float* Km;        // [BH][Tp][Tp] or null: K[t][s] = c_s (dY_t . g_s)(x_t . x_s), s < t (may be xx: each element is read first)
   float* Fm;        // [BH][Tp][Tp] or null: F[t][s], s < t (may be gy, alike)
+  const void* X;    // inputs of the kernel that contracts both products itself
+  const void* G;
+  const void* dY;
+  int64_t d, m;
 };
 
 template <int FMODE>
@@ -545,6 +549,117 @@ static __global__ void __launch_bounds__(256) wide_deta_kernel(const WDetaArgs a
 #pragma unroll
     for (int i = 1; i < 32; ++i) v += part[half][i][g];
     *reinterpret_cast<f32x4*>(a.dpart + ((bh * 2 * Kp) + 2 * tb + half) * a.Tp + BT * sb + 32 * quarter + 4 * g) = v;
+  }
+}
+
+// The same for a call that wants deta of the gate gradients only and no read
+// (whose scores would leave dY G^T): one workgroup per tile contracts both
+// products into two accumulators, in one launch after the gates' instead of
+// three.  Column sums over the rows t of each wave's 64-row half.
+template <class OP, int FMODE>
+static __global__ void __launch_bounds__(256) wide_deta_pair_kernel(const WDetaArgs a) {
+  typedef typename OP::elem E;
+  typedef typename OP::frag F;
+  constexpr int BT = 128, BK = 64, NT = 256;
+  __shared__ __attribute__((aligned(16))) E Ps[BT * BK];
+  __shared__ __attribute__((aligned(16))) E Qs[BT * BK];
+
+  const int64_t Kp = a.Tp / BT, per_seq = Kp * (Kp + 1) / 2;
+  const int64_t bh = blockIdx.x / per_seq;
+  int64_t tb, sb;
+  tri_tile(blockIdx.x % per_seq, tb, sb);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wt = w >> 1, ws = w & 1;
+  const int c = lane & 15, q = lane >> 4;
+  const size_t es = sizeof(E);
+
+  f32x4 acc[2][4][4];  // [contraction][s block][t block]: 0: dY_t . g_s, 1: x_t . x_s
+#pragma unroll
+  for (int z = 0; z < 2; ++z)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[z][i][j] = zero4();
+
+#pragma unroll
+  for (int z = 0; z < 2; ++z) {
+    const int64_t w_ = z == 0 ? a.m : a.d;
+    const rsrc_t Qr = make_rsrc(static_cast<const E*>(z == 0 ? a.dY : a.X) + bh * a.T * w_, (uint32_t)(a.T * w_ * es));
+    const rsrc_t Kr = make_rsrc(static_cast<const E*>(z == 0 ? a.G : a.X) + bh * a.T * w_, (uint32_t)(a.T * w_ * es));
+    const uint32_t stride = (uint32_t)(w_ * es);
+    const uint32_t qoff = (uint32_t)(BT * tb * stride), koff = (uint32_t)(BT * sb * stride);
+    GTile<E, BT, BK, NT> qt, kt;
+    qt.load(Qr, qoff, stride, 0, tid);
+    kt.load(Kr, koff, stride, 0, tid);
+    for (int64_t k0 = 0; k0 < w_; k0 += BK) {
+      __syncthreads();
+      qt.store(Qs, tid);
+      kt.store(Ps, tid);
+      __syncthreads();
+      const bool more = k0 + BK < w_;
+      qt.load(Qr, more ? qoff : kOOB, stride, (uint32_t)((k0 + BK) * es), tid);
+      kt.load(Kr, more ? koff : kOOB, stride, (uint32_t)((k0 + BK) * es), tid);
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 32) {
+        F qf[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) qf[j] = OP::load_n_sep(Qs, BK, 64 * wt + 16 * j, kk, lane);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const F pf = OP::load_n_sep(Ps, BK, 64 * ws + 16 * i, kk, lane);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[z][i][j] = OP::mma(acc[z][i][j], pf, qf[j]);
+        }
+      }
+    }
+  }
+
+  // Lane (c, q) of block (i, j): s = s0 + 16 i + 4 q + r, t = t0 + 16 j + c.
+  const int64_t s0 = BT * sb + 64 * ws, t0 = BT * tb + 64 * wt;
+  const int* zc = a.zc + bh * a.Tp;
+  const double* lc = a.lc + bh * a.Tp;
+  const double ref = FMODE == 2 ? lc[s0 + 63] : 0.0;
+  float col[4][4];  // [i][r]: this lane's partial column sums
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) col[i][r] = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int64_t t = t0 + 16 * j + c;
+    int zt = 0;
+    float at = 0.f;
+    if (FMODE >= 1 && t >= 1) zt = zc[t - 1];
+    if (FMODE == 2 && t >= 1) at = (float)(lc[t - 1] - ref);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t s = s0 + 16 * i + 4 * q;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool live = s + r < t && t < a.T;
+        float f = live ? 1.f : 0.f;
+        const int zs = FMODE >= 1 ? zc[s + r] : 0;
+        if (FMODE >= 1 && (zs >> 1) != (zt >> 1)) f = 0.f;
+        if (FMODE == 2 && f != 0.f) f = ((zs ^ zt) & 1 ? -1.f : 1.f) * expf(at + (float)(ref - lc[s + r]));
+        col[i][r] += f * (live ? acc[0][i][j][r] * acc[1][i][j][r] : 0.f);
+      }
+    }
+  }
+  // Sum over the 16 rows t held by lanes c = 0..15, then write this wave's
+  // 64-row partial for its 64 columns.
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float v = col[i][r];
+#pragma unroll
+      for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 16);
+      col[i][r] = v;
+    }
+  if (c == 0) {
+    float* out = a.dpart + ((bh * 2 * Kp) + 2 * tb + wt) * a.Tp;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<f32x4*>(out + s0 + 16 * i + 4 * q) = f32x4{col[i][0], col[i][1], col[i][2], col[i][3]};
   }
 }
 
@@ -1166,6 +1281,26 @@ hipError_t launch_wide_fwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
   return p.bf16 ? wide_run<OpBF16>(p, f, false, f.Y, nullptr, s) : wide_run<OpF32>(p, f, false, f.Y, nullptr, s);
 }
 
+// Whether deta without a read is contracted tile by tile (wide_deta_pair_kernel)
+// instead of by split score launches and a stream over them.  In steps of 64 of a
+// width: a workgroup per tile takes them all, 256 tiles at once; a score launch
+// takes its share of the split, 128 workgroups at once as measured, and dG's, when
+// split, leaves X X^T behind.  The two launches more are worth 11 bf16 steps, no
+// fp32 one.  Chosen so, 203 calls of 1 to 640 tiles and 6 to 80 steps are at most
+// 12 % (fp32: 0) off the better way (bf16, 192 tiles of 512 -> 512: 39 us against
+// 56 split; 72 of 1024 -> 4096 80 steps long: 66 us split against 88).
+static bool wide_deta_pair(const WideProblem& p, bool dg) {
+  const int64_t BH = p.B * p.H, Kp = p.Tp / 128;
+  const double tiles = (double)(BH * Kp * (Kp + 1) / 2);
+  auto rounds = [](double n, double at_once) { return n > at_once ? n / at_once : 1.0; };
+  auto score = [&](int w) {
+    const int k = wide_score_splits(BH, p.Tp, w);
+    return w / 64.0 / k * rounds(tiles * k, 128);
+  };
+  const double xx = dg && wide_score_splits(BH, p.Tp, p.d) > 1 ? 0.0 : score(p.d);
+  return (p.d + p.m) / 64.0 * rounds(tiles, 256) <= xx + score(p.m) + (p.bf16 ? 11 : 0);
+}
+
 // The backward of a wide map, each output when requested:
 //   gtilde = dY W_0 + S_read X        (causal; S_read = F c (dY G^T))
 //   dX     = gtilde + S_read^T X      (anti-causal, write side)
@@ -1177,6 +1312,8 @@ static hipError_t wide_bwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
   const int64_t BH = p.B * p.H;
   const WideWs ws = wide_ws(p, f.ws);
   const bool gates = f.deta || f.dalpha;
+  const int64_t Kp = p.Tp / 128, tiles = BH * Kp * (Kp + 1) / 2;
+  const bool pair = f.deta && !f.dalpha && !f.gtilde && !f.dX && wide_deta_pair(p, f.dG != nullptr);
   // The gate gradients' dY G^T, kept unscaled beside the read's scores.
   float* const gy = gates ? ws.Fm : nullptr;
   if (f.gtilde || f.dX) {
@@ -1192,7 +1329,7 @@ static hipError_t wide_bwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
   } else if (f.dG || gates) {
     const WGateArgs g = gate_args(p, f, ws);
     timing_begin(GRADLEV_K_WIDE_SCORE, s);
-    if (gates) wide_scores<OP>(p, ws, f.dY, f.G, p.m, false, gy, &g, s);
+    if (gates && !pair) wide_scores<OP>(p, ws, f.dY, f.G, p.m, false, gy, &g, s);
     else hipLaunchKernelGGL(wide_gate_kernel, dim3((unsigned)BH), dim3(256), 0, s, g);
     timing_end(GRADLEV_K_WIDE_SCORE, s);
   }
@@ -1210,22 +1347,19 @@ static hipError_t wide_bwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
     // X X^T as the partials of a split contraction (still there after dG's
     // scores), or whole in the score region, which is free from here on: the
     // K tiles of dalpha take it too, and its F tiles the place of dY G^T.
-    if (ks == 1) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, ws.Km, nullptr, s);
-    else if (!f.dG) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, nullptr, nullptr, s);
+    if (!pair && ks == 1) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, ws.Km, nullptr, s);
+    else if (!pair && !f.dG) wide_scores<OP>(p, ws, f.X, f.X, p.d, false, nullptr, nullptr, s);
     WDetaArgs da{p.T, p.Tp, BH, p.H, ws.zc, ws.lc, ws.dpart, f.reset, ws.cw, gy, ks == 1 ? ws.Km : ws.part, ks,
-                 f.dalpha ? ws.Km : nullptr, f.dalpha ? ws.Fm : nullptr};
-    const int64_t Kp = p.Tp / 128;
-    const unsigned grid = (unsigned)(BH * Kp * (Kp + 1) / 2);
+                 f.dalpha ? ws.Km : nullptr, f.dalpha ? ws.Fm : nullptr, f.X, f.G, f.dY, p.d, p.m};
     const unsigned rgrid = (unsigned)((BH * p.T + 255) / 256);
-    if (p.fmode == 0) hipLaunchKernelGGL((wide_deta_kernel<0>), dim3(4 * grid), dim3(256), 0, s, da);
-    else if (p.fmode == 1) hipLaunchKernelGGL((wide_deta_kernel<1>), dim3(4 * grid), dim3(256), 0, s, da);
-    else hipLaunchKernelGGL((wide_deta_kernel<2>), dim3(4 * grid), dim3(256), 0, s, da);
+    auto run = [&](auto k0, auto k1, auto k2, int64_t grid) {
+      hipLaunchKernelGGL(p.fmode == 0 ? k0 : p.fmode == 1 ? k1 : k2, dim3((unsigned)grid), dim3(256), 0, s, da);
+    };
+    if (pair) run(wide_deta_pair_kernel<OP, 0>, wide_deta_pair_kernel<OP, 1>, wide_deta_pair_kernel<OP, 2>, tiles);
+    else run(wide_deta_kernel<0>, wide_deta_kernel<1>, wide_deta_kernel<2>, 4 * tiles);
     if (f.deta) hipLaunchKernelGGL(wide_colsum_reduce, dim3(rgrid), dim3(256), 0, s, da, f.deta, -1.f);
     if (f.dalpha) {
-      const unsigned dgrid = (unsigned)(BH * Kp * (2 * Kp + 1));  // 64 x 64 tiles
-      if (p.fmode == 0) hipLaunchKernelGGL((wide_dalpha_kernel<0>), dim3(dgrid), dim3(256), 0, s, da);
-      else if (p.fmode == 1) hipLaunchKernelGGL((wide_dalpha_kernel<1>), dim3(dgrid), dim3(256), 0, s, da);
-      else hipLaunchKernelGGL((wide_dalpha_kernel<2>), dim3(dgrid), dim3(256), 0, s, da);
+      run(wide_dalpha_kernel<0>, wide_dalpha_kernel<1>, wide_dalpha_kernel<2>, BH * Kp * (2 * Kp + 1));  // 64 x 64 tiles
       hipLaunchKernelGGL(wide_colsum_reduce, dim3(rgrid), dim3(256), 0, s, da, f.dalpha, 1.f);
     }
     timing_end(GRADLEV_K_WIDE_SCORE, s);

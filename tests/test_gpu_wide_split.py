@@ -43,3 +43,22 @@ def test_wide_unread_step_size(T):
     got = gl.scan_bwd_gated(W0, X, G, dY, e, a, r, outputs=WIDE_BWD)
     for k in WIDE_BWD:
         np.testing.assert_array_equal(to_host(got[k]), to_host(ref[k]), err_msg=k)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T", [1, 129, 300])
+@pytest.mark.parametrize("alpha_kind,with_reset", [("1", False), ("1", True), ("signed", True)])
+def test_wide_deta_alone(dtype, T, alpha_kind, with_reset):
+    """Without a read: one workgroup per tile contracts both products (narrow maps)."""
+    log(f"wide deta alone dtype={dtype} T={T} alpha={alpha_kind} reset={with_reset}")
+    inp = inputs(2, 2, T, 128, 256, dtype, seed=T, alpha_kind=alpha_kind, eta_kind="token", with_reset=with_reset)
+    W0, X, G, dY, e, a, r = dev_inputs(inp, dtype)
+    ref = orc.scan_bwd(inp["W0"], inp["X"], inp["G"], inp["eta"], inp["dY"], alpha=inp["alpha"], reset=inp["reset"])
+    got = {k: gl.scan_bwd_gated(W0, X, G, dY, e, a, r, outputs=o) for k, o in (("deta", ("deta",)), ("dg", ("deta", "dg")))}
+    check("deta", to_host(got["deta"]["deta"]), ref["deta"], dtype)
+    check("dg", to_host(got["dg"]["dg"]), ref["dg"], dtype)
+    np.testing.assert_array_equal(to_host(got["dg"]["deta"]), to_host(got["deta"]["deta"]))
+    e = e.clone()
+    e[..., -1] = float("inf")  # no token reads the last one's write
+    again = gl.scan_bwd_gated(W0, X, G, dY, e, a, r, outputs=("deta",))["deta"]
+    np.testing.assert_array_equal(to_host(again), to_host(got["deta"]["deta"]))
