@@ -1120,10 +1120,9 @@ size_t wide_workspace_bytes(const WideProblem& p) {
   const int kd = wide_score_splits((int64_t)BH, (int64_t)Tp, p.d), km = wide_score_splits((int64_t)BH, (int64_t)Tp, p.m);
   const int ks = kd > km ? kd : km;  // the forward contracts over d, the read over m
   const size_t part = ks > 1 ? (size_t)ks * BH * Tp * Tp * 4 : 0;
-  const size_t planes = p.bf16 ? (size_t)p.H * p.m * p.d * 4 : 0;  // not used: callers' sizes include it
-  const size_t dpart = BH * 2 * (Tp / 128) * Tp * 4;               // partial column sums (deta, dalpha)
-  const size_t fm = BH * Tp * Tp * 4;                              // dalpha: fp32 F tiles
-  return (gates + 255) / 256 * 256 + (S + 255) / 256 * 256 + (part + 255) / 256 * 256 + (planes + 255) / 256 * 256 +
+  const size_t dpart = BH * 2 * (Tp / 128) * Tp * 4;  // partial column sums (deta, dalpha)
+  const size_t fm = BH * Tp * Tp * 4;                 // dY G^T, then dalpha's fp32 F tiles
+  return (gates + 255) / 256 * 256 + (S + 255) / 256 * 256 + (part + 255) / 256 * 256 +
          (dpart + 255) / 256 * 256 + fm;
 }
 
@@ -1156,8 +1155,7 @@ WideWs wide_ws(const WideProblem& p, void* ws) {
   o.part = reinterpret_cast<float*>(pt);
   const int kd = wide_score_splits((int64_t)BH, (int64_t)Tp, p.d), km = wide_score_splits((int64_t)BH, (int64_t)Tp, p.m);
   const int ks = kd > km ? kd : km;
-  char* dp = pt + ((ks > 1 ? (size_t)ks * BH * Tp * Tp * 4 : 0) + 255) / 256 * 256 +
-             ((p.bf16 ? (size_t)p.H * p.m * p.d * 4 : 0) + 255) / 256 * 256;
+  char* dp = pt + ((ks > 1 ? (size_t)ks * BH * Tp * Tp * 4 : 0) + 255) / 256 * 256;
   o.dpart = reinterpret_cast<float*>(dp);
   o.Fm = reinterpret_cast<float*>(dp + (BH * 2 * (Tp / 128) * Tp * 4 + 255) / 256 * 256);
   return o;
