@@ -176,7 +176,13 @@ bwd_main_kernel(const BArgs a) {
   // and Rj[ib] holds R[i][j = 16w + c], at the segment's end: W_0 - sum_{j<=seg} A_j
   // (subtracted in segment order) and R = sum_{j>seg} B_j (added from the last segment down).
   f32x4 Wj[NWB][IB], Rj[IB];
-  constexpr int PU = NWB * IB <= 4 ? 4 : 2;  // aggregates summed per batch of loads (register budget)
+  // Aggregates summed per batch of loads: few enough that the prologue does not
+  // decide the registers, and with them the workgroups on a CU (read of 96
+  // sequences, 128 x 64 bf16: 63 us with batches of four, 52 with two).  CLAMP:
+  // the one kernel whose loop, beside sums in two phases, no longer fits the 128
+  // registers of two workgroups (96 sequences of 2048: 109 against 89 us).
+  constexpr bool CLAMP = FULL && !ETAV && OP::kSplit == 2 && D == 128 && M == 64;
+  constexpr int PU = FULL ? (NWB * IB <= 4 ? 4 : 2) : (IB <= 4 ? 2 : 1);
   if (w < JB) {
     // The segment's end state: saved by the forward, or W_0 minus the
     // aggregated writes up to and including this segment.
@@ -190,7 +196,7 @@ bwd_main_kernel(const BArgs a) {
         for (int r = 0; r < 4; ++r) ws[e * IB + ib][r] = w0[(int64_t)(16 * ib + 4 * q + r) * D + 16 * blk(e) + c];
     const int64_t o = bh * a.nseg * M * D + 4 * q;
     const float* A = a.aggA + o + (int64_t)(16 * blk(0) + c) * M;  // column block e lies 16 M floats after e - 1
-    sum_segments<PU, true>(ws, a.wend ? 0 : (int)seg + 1, [&](int k) { return A + (int64_t)k * M * D; },
+    sum_segments<PU, true, CLAMP>(ws, a.wend ? 0 : (int)seg + 1, [&](int k) { return A + (int64_t)k * M * D; },
                            [](int i) { return i / IB * 16 * M + i % IB * 16; });
 #pragma unroll
     for (int e = 0; e < NWB; ++e)
@@ -200,7 +206,7 @@ bwd_main_kernel(const BArgs a) {
     for (int ib = 0; ib < IB; ++ib) Rj[ib] = zero4();
     if (FULL && a.aggB && !no_sfx) {
       const float* Bk = a.aggB + o + (int64_t)(16 * w + c) * M;
-      sum_segments<IB <= 4 ? 4 : 2, false>(Rj, (int)(j_last - seg), [&](int k) { return Bk + (j_last - k) * M * D; },
+      sum_segments<IB <= 4 ? 4 : 2, false, CLAMP>(Rj, (int)(j_last - seg), [&](int k) { return Bk + (j_last - k) * M * D; },
                                            [](int ib) { return 16 * ib; });
     }
   }

@@ -314,21 +314,23 @@ __device__ __forceinline__ int64_t first_reset_in(rsrc_t row, int64_t lo, int64_
 // loads issued for every batch but added behind a branch, the compiler moved
 // each load into its branch, where it is waited for alone (backward of 16
 // sequences of 8192 tokens in 16 segments, 64 x 64 bf16: 70 us, so 57).
-template <int PU, bool SUB, int N, class P, class AT>
+template <int PU, bool SUB, bool CLAMP = false, int N, class P, class AT>
 __device__ __forceinline__ void sum_segments(f32x4 (&s)[N], int n, P p, AT at) {
-  auto batch = [&](int k, auto full) {
-    constexpr bool FULL = decltype(full)::value != 0;
+  // The segments from k on: all PU of them, or (REST) those below n; with
+  // CLAMP the loads past them read the last one again.
+  auto batch = [&](int k, auto rest) {
+    constexpr bool REST = decltype(rest)::value != 0;
     f32x4 v[PU][N];
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
-      if (!FULL && k + u >= n) break;
-      const float* b = p(k + u);
+      if (REST && !CLAMP && k + u >= n) break;
+      const float* b = p(CLAMP && k + u >= n ? n - 1 : k + u);
 #pragma unroll
       for (int i = 0; i < N; ++i) v[u][i] = *reinterpret_cast<const f32x4*>(b + at(i));
     }
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
-      if (!FULL && k + u >= n) break;
+      if (REST && k + u >= n) break;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         if constexpr (SUB) s[i] -= v[u][i];
@@ -336,9 +338,13 @@ __device__ __forceinline__ void sum_segments(f32x4 (&s)[N], int n, P p, AT at) {
       }
     }
   };
-  int k = 0;
-  for (; k + PU <= n; k += PU) batch(k, IntC<1>{});
-  if (k < n) batch(k, IntC<0>{});
+  if constexpr (CLAMP) {
+    for (int k = 0; k < n; k += PU) batch(k, IntC<1>{});
+  } else {
+    int k = 0;
+    for (; k + PU <= n; k += PU) batch(k, IntC<0>{});
+    if (k < n) batch(k, IntC<1>{});
+  }
 }
 
 // ---------------------------------------------------------------------------
