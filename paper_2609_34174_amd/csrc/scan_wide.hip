@@ -1280,23 +1280,23 @@ hipError_t launch_wide_fwd(const WideProblem& p, const WidePtrs& f, hipStream_t 
 }
 
 // Whether deta without a read is contracted tile by tile (wide_deta_pair_kernel)
-// instead of by split score launches and a stream over them.  In steps of 64 of a
-// width: a workgroup per tile takes them all, 256 tiles at once; a score launch
-// takes its share of the split, 128 workgroups at once as measured, and dG's, when
-// split, leaves X X^T behind.  The two launches more are worth 11 bf16 steps, no
-// fp32 one.  Chosen so, 203 calls of 1 to 640 tiles and 6 to 80 steps are at most
-// 12 % (fp32: 0) off the better way (bf16, 192 tiles of 512 -> 512: 39 us against
-// 56 split; 72 of 1024 -> 4096 80 steps long: 66 us split against 88).
+// instead of by split score launches and a stream over them, in steps of 64 of a
+// width: a workgroup per tile takes them all, in rounds of 256; a score launch
+// takes its share of the split, and dG's, when split, leaves X X^T behind.  The
+// launches more and the stream are worth 11.5 bf16 steps and one for 25 tiles (4
+// fewer beside dG), 6 fp32 ones.  Chosen so, 432 calls of 1 to 640 tiles and 6 to
+// 80 steps are at most 8 % off the better way (bf16, 192 tiles of 512 -> 512: 39
+// us against 56 split; 72 of 1024 -> 4096: 66 us split against 88).
 static bool wide_deta_pair(const WideProblem& p, bool dg) {
-  const int64_t BH = p.B * p.H, Kp = p.Tp / 128;
-  const double tiles = (double)(BH * Kp * (Kp + 1) / 2);
-  auto rounds = [](double n, double at_once) { return n > at_once ? n / at_once : 1.0; };
+  const int64_t BH = p.B * p.H, Kp = p.Tp / 128, tiles = BH * Kp * (Kp + 1) / 2;
   auto score = [&](int w) {
-    const int k = wide_score_splits(BH, p.Tp, w);
-    return w / 64.0 / k * rounds(tiles * k, 128);
+    const int64_t k = wide_score_splits(BH, p.Tp, w), n = tiles * k;
+    const double rounds = !p.bf16 ? (double)((n + 255) / 256) : n > 192 ? n / 192.0 : 1.0;
+    return w / 64.0 / k * rounds;
   };
   const double xx = dg && wide_score_splits(BH, p.Tp, p.d) > 1 ? 0.0 : score(p.d);
-  return (p.d + p.m) / 64.0 * rounds(tiles, 256) <= xx + score(p.m) + (p.bf16 ? 11 : 0);
+  const double more = p.bf16 ? 11.5 + tiles / 25.0 - (dg ? 4 : 0) : 6;
+  return (p.d + p.m) / 64.0 * ((tiles + 255) / 256) <= xx + score(p.m) + more;
 }
 
 // The backward of a wide map, each output when requested:
