@@ -310,10 +310,12 @@ __device__ __forceinline__ int64_t first_reset_in(rsrc_t row, int64_t lo, int64_
 
 // s[i] += (SUB: -=) the aggregates of n segments, the k-th at p(k) + at(i)
 // floats, in order, PU segments' loads in flight together.  A whole batch has
-// no branch, the remainder branches around both its loads and its adds: with
-// loads issued for every batch but added behind a branch, the compiler moved
-// each load into its branch, where it is waited for alone (backward of 16
-// sequences of 8192 tokens in 16 segments, 64 x 64 bf16: 70 us, so 57).
+// no branch, the remainder branches around both its loads and its adds.  With
+// CLAMP every batch issues all its loads and branches around adds past the
+// last one: a little faster where the compiler leaves it so (forward of 256
+// sequences of 2048: 51.5 -> 50.6 us), but in some of the backward's kernels it
+// moved each load into its add's branch, where it is waited for alone (16
+// sequences of 8192 tokens in 16 segments, 64 x 64 bf16: 70 us against 57).
 template <int PU, bool SUB, bool CLAMP = false, int N, class P, class AT>
 __device__ __forceinline__ void sum_segments(f32x4 (&s)[N], int n, P p, AT at) {
   // The segments from k on: all PU of them, or (REST) those below n; with

@@ -133,7 +133,7 @@ fwd_main_kernel(const KArgs a) {
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb) W0r[jb] = Ws[jb];
     const float* ag = a.aggA + bh * a.nseg * M * D + o;
-    sum_segments<4, true>(Ws, from_w0 ? 0 : (int)(seg - j_first), [&](int k) { return ag + (j_first + k) * M * D; },
+    sum_segments<4, true, true>(Ws, from_w0 ? 0 : (int)(seg - j_first), [&](int k) { return ag + (j_first + k) * M * D; },
                           [](int jb) { return 16 * jb; });
   }
   if constexpr (!RS)
