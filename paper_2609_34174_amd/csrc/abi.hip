@@ -53,8 +53,11 @@ struct Plan {
 // ceil(256 w / BH) segments for w workgroups a CU this takes a fifth off the
 // geometric mean over 1 to 256 sequences of 128 to 8000 tokens at the worst
 // widths (bf16 128 x 128 forward) and 4 % at the best.
-// Aggregates (two of `md` bytes per segment, one more per sequence) stay within
-// the static scratch where one segment would not do, so that no call outgrows it.
+// More than one segment is taken only while two aggregates of `md` bytes each and
+// one more per sequence - what a plain backward keeps - fit the static scratch:
+// that bounds what parallel segments add to a workspace.  (A forward keeps one per
+// segment, the gated backward three beside its chunk-start states; one segment's
+// may outgrow the scratch by themselves.)
 int64_t pick_seg_chunks(int64_t BH, int64_t T, int C, size_t md, const SegCost& c, int64_t hint) {
   const int64_t nchunks = (T + C - 1) / C;
   if (hint > 0) return (hint + C - 1) / C;

@@ -42,10 +42,13 @@ fwd_main_kernel(const KArgs a) {
   constexpr int NW = cmax(D, M) / 16, NT = NW * 64;
   constexpr int TB = C / 16, JB = D / 16, IB = M / 16;
   constexpr bool SPLITV = ETAV && OP::kSplit == 2;
-  // Two buffers of the chunk's tiles, used in turn, where they fit beside a
-  // second workgroup: a wave stages the next chunk while others still compute
-  // this one, with one barrier per chunk instead of two (long-bf16 forward 130
-  // -> 128 us, stack-bf16 57.4 -> 56.8 us, lm-bf16 with documents 42.4 -> 42.0 us).
+  // Two buffers of the chunk's tiles, used in turn: a wave stages the next
+  // chunk while others still compute this one, with one barrier per chunk
+  // instead of two (long-bf16 forward 130 -> 128 us; 64 x 64 maps within noise:
+  // stack-bf16 57.4 -> 56.8 us, lm-bf16 with documents 42.4 -> 42.0 us).  They
+  // shut no workgroup out: 64 x 64 maps keep two or three on a CU (33 to 50 KB),
+  // and a 128-wide side's eight waves of 183 to 246 registers leave no room for a
+  // second one whatever the LDS (up to 98 KB, 128 x 128 with per-token eta).
   constexpr bool DB = OP::kSplit == 2 && C == 64;
   __shared__ E Xs_[DB ? 2 : 1][C * D];    // X[t][j]
   __shared__ E Gs_[DB ? 2 : 1][C * M];    // G[t][i]
@@ -387,7 +390,8 @@ int fwd_chunk_for(int bf16, int d, int m, int requested) {
 
 // Fitted to both launches' times over 1 to 256 sequences of 128 to 8000 tokens
 // in every segmentation (bf16: 5-6 % rms; the fp32 and mixed widths from fewer
-// points).  A 64 x 64 workgroup leaves room for a second one on its CU, which
+// points).  The prologues, aggregate passes and fp32 kernels have become faster
+// since; what is weighed against each other, not the microseconds, still holds.  A 64 x 64 workgroup leaves room for a second one on its CU, which
 // costs 0.72 of the first with inputs from the cache, but 1.2 times it from
 // HBM at the sizes that fill the chip (B=4, H=32, T=4096: four segments 246 us
 // a step, two 232 us: fewer concurrent streams).  The table's 2.2 for the pair

@@ -464,7 +464,7 @@ static __global__ void __launch_bounds__(256) wide_score_finish(const WScoreArgs
 // which zeroes the tokens a reset overrides.  (One workgroup per tile doing
 // both contractions itself took 85 us at B=2, T=1024, 1024 -> 4096: 72
 // workgroups, each 80 steps long; the score kernel's split ranges do X X^T in
-// 14 to 42 us and this stream takes 5 us.)
+// 14 to 42 us and this stream 12 us, the K and F tiles' stores included.)
 // Workgroup: 32 columns of one tile (4 per tile); thread: 4 columns of every
 // 32nd row.
 // ---------------------------------------------------------------------------

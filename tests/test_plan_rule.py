@@ -21,6 +21,24 @@ def test_automatic_segments(dtype, d, m, BH):
         assert p.workspace_bytes <= max(gl.STATIC_SCRATCH_BYTES, one) + 3 * 256
 
 
+@pytest.mark.parametrize("dtype", [gl.BF16, gl.F32])
+@pytest.mark.parametrize("d,m", [(64, 64), (64, 128), (128, 128)])
+@pytest.mark.parametrize("BH", [1, 8, 33, 257, 4096])
+def test_workspace_of_every_plan(dtype, d, m, BH):
+    """Saved, gated and gated saved plans: aggregates of parallel segments within
+    the scratch each, chunk-start states and a single segment's sums beside them."""
+    for T in (64, 1000, 8192, 60000):
+        s = gl.make_shape(B=BH, H=1, T=T, d_in=d, d_out=m, dtype=dtype)
+        md, gates, slack = BH * d * m * 4, BH * 16 * 4, 8 * 256
+        agg = max(gl.STATIC_SCRATCH_BYTES, 3 * md)  # A, B per segment and one sum per sequence
+        saved, ws = gl.saved_bytes(s)
+        assert ws <= agg + slack and saved <= agg
+        states = md * ((T + 31) // 32)  # 32- or 64-token tiles
+        gated_saved, gated_ws = gl.gated_saved_bytes(s)
+        assert gated_saved <= states and gated_ws <= 1.5 * agg + gates + slack
+        assert gl.gated_workspace_bytes(s) <= 1.5 * agg + states + gates + slack
+
+
 # Forward + backward of the bf16 reset pair, us by segments per sequence (64 x 64,
 # scalar eta, documents of mean length 200), measured on an MI355X.
 RESET_US = {
