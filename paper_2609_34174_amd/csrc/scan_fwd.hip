@@ -399,13 +399,14 @@ int fwd_chunk_for(int bf16, int d, int m, int requested) {
 // one after the other.  The bf16 reset pair (whose forward keeps chunk states and restarts
 // within chunks) is fitted by its choices: both calls over 1 to 400 sequences of
 // 300 to 8000 tokens without resets and with mean documents of 200 and 1000 in up
-// to nine segmentations each, 96 shapes, are on average within 1 % of the best one
+// to nine segmentations each, 96 shapes, are on average within 2 % of the best one
 // (with the plain costs 3.4 % off at 200, up to 24 %; 8 sequences of 2000 got 8
-// segments where 16 are best, 64.2 against 56.8 us).  fp32's plain costs choose
-// within 1 % of the best for its reset pair as they are.
+// segments where 16 are best, 64.2 against 56.8 us).  Its pair is the HBM-resident
+// one too (128 of 2048 from HBM: two segments 157.7 us a step, four 161.2).  fp32's
+// plain costs choose within 1 % of the best for its reset pair as they are.
 SegCost fwd_seg_cost(int bf16, int d, int m, bool reset) {
   const int wide = (d == 128) + (m == 128);
-  if (bf16 && reset) return {9.0f, 11.0f, 0.83f, 4.9f, 0.36f, 1.2f, 2, 1.37f};
+  if (bf16 && reset) return {9.0f, 11.0f, 0.83f, 4.9f, 0.36f, 1.2f, 2, 2.4f};
   static const SegCost bf[3] = {{1.6f, 4.0f, 0.55f, 1.8f, 0.47f, 1.4f, 2, 2.2f},
                                 {0.f, 4.4f, 0.83f, 3.1f, 0.86f, 2.0f, 1, 0.f},
                                 {0.f, 5.9f, 1.0f, 2.6f, 1.72f, 2.9f, 1, 0.f}};
