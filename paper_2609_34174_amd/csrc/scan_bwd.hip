@@ -180,8 +180,9 @@ bwd_main_kernel(const BArgs a) {
   // decide the registers, and with them the workgroups on a CU (read of 96
   // sequences, 128 x 64 bf16: 63 us with batches of four, 52 with two).  CLAMP:
   // the one kernel whose loop, beside sums in two phases, no longer fits the 128
-  // registers of two workgroups (96 sequences of 2048: 109 against 89 us).
-  constexpr bool CLAMP = FULL && !ETAV && OP::kSplit == 2 && D == 128 && M == 64;
+  // registers of two workgroups (96 sequences of 2048: 109 against 89 us), and
+  // the reset pair's (128 of 4096, a step: 256 against 252 us).
+  constexpr bool CLAMP = RST || (FULL && !ETAV && OP::kSplit == 2 && D == 128 && M == 64);
   constexpr int PU = FULL ? (NWB * IB <= 4 ? 4 : 2) : (IB <= 4 ? 2 : 1);
   if (w < JB) {
     // The segment's end state: saved by the forward, or W_0 minus the
